@@ -19,6 +19,8 @@
 // when C_in = 16 so that TP*C_in is a multiple of 32; the extra tap is zero).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "internal.h"
 #include "mfma_util.h"
 #include "wsnet_internal.h"
@@ -31,7 +33,11 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kTile = 64;     // positions per conv workgroup
-constexpr int kWP = 128;      // positions per weight-gradient workgroup
+constexpr int kWP = 128;      // positions per weight-gradient chunk
+// Weight-gradient partials per layer: as many workgroups as CUs (twice as
+// many channel slices in the 64 -> 64 layers), each adding its chunks up, so
+// that writing and adding the partials stays a fraction of reading x and g.
+constexpr int kWgGroups = 256, kWgGroups64 = 128;
 
 __device__ inline f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -111,84 +117,213 @@ __global__ __launch_bounds__(256) void k_conv(int M, const __bf16* __restrict__ 
 }
 
 // ---------------------------------------------------------------------------
-// weight gradient partials: part[wg][o][t][c] = sum over the workgroup's
-// positions p of g[p][o] * x[p + t - 2][c];  bpart[wg][o] = sum_p g[p][o].
+// Weight gradient, dW[o][t][c] = sum_p g[p][o] x[p + t - 2][c], a GEMM over
+// the positions.  Workgroup (grp, slice) takes every gridDim.x-th chunk of
+// kWP positions and the OH output channels of its slice.  A chunk is staged
+// in LDS by channel (position pairs as 32-bit words, so a wave's stores fall
+// on consecutive banks); the next chunk's rows load meanwhile.  A wave owns
+// one 16-channel tile of x, TOW tiles of g and every WT-th tap: it reads the
+// 16 positions pk .. pk + 15 of its x row once and cuts the five shifted
+// operands out of them, so one pair of LDS reads feeds 5 TOW MFMAs.  A
+// chunk's products accumulate in FP32 (kWP terms), chunks in double:
+// part[grp][o][t][c], with bpart[grp][o] = sum_p g[p][o].
+// Bound: the reads of x and g.  At 64 pairs of 2048 positions, 64 -> 64
+// channels, FP32 partials per 128 positions (1024 of 96 KiB) and a serial sum
+// over them took 53 us + 305 us; see kWgGroups for the partial count.
 // ---------------------------------------------------------------------------
-template <int CIN, int COUT>
-__global__ __launch_bounds__(256) void k_wgrad(int M, const __bf16* __restrict__ x,
+template <int CIN, int COUT, int OH>
+__global__ __launch_bounds__(512) void k_wgrad(int M, int nch, int cpr, const __bf16* __restrict__ x,
                                                const __bf16* __restrict__ g,
-                                               float* __restrict__ part,
-                                               float* __restrict__ bpart) {
-  constexpr int TP = taps_pad<CIN>();
-  constexpr int LDG = kWP + 8;
-  constexpr int LDI = kWP + 8 + 8;            // kWP + TP - 1 staged positions, padded
-  constexpr int TO = COUT / 16, TC = TP * CIN / 16, NT = TO * TC;
-  __shared__ __align__(16) __bf16 gT[COUT * LDG];
-  __shared__ __align__(16) __bf16 xT[CIN * LDI];
+                                               double* __restrict__ part,
+                                               double* __restrict__ bpart) {
+  constexpr int LDP = kWP + 8;            // row stride: kWP + 4 staged positions of x, 16-byte rows
+  constexpr int WC = CIN / 16, TO = OH / 16;
+  constexpr int WO = TO < 8 / WC ? TO : 8 / WC, TOW = TO / WO, WT = 8 / (WC * WO);
+  constexpr int NTW = (5 + WT - 1) / WT;  // taps per wave
+  constexpr int GI = (kWP / 2) * (OH / 8), NGI = (GI + 511) / 512;
+  constexpr int XP = kWP / 2 + 2, XI = XP * (CIN / 8), NXI = (XI + 511) / 512;
+  constexpr int BS = 512 / OH, BP = kWP / BS;  // bias: threads per channel, positions per thread
+  static_assert(WC * WO * WT == 8 && TOW * WO == TO, "waves");
+  static_assert(BP % 8 == 0 || BP == 4, "bias positions");
+  __shared__ __align__(16) __bf16 gT[OH * LDP];
+  __shared__ __align__(16) __bf16 xT[CIN * LDP];
+  __shared__ double bs[512];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.y, p0 = blockIdx.x * kWP;
-  const int wg = blockIdx.y * gridDim.x + blockIdx.x;
-  const int np = min(kWP, M - p0);
-  const __bf16* gb = g + (size_t)b * M * COUT;
-  const __bf16* xb = x + (size_t)b * M * CIN;
-  for (int e = tid; e < kWP * COUT; e += 256) {
-    const int p = e / COUT, o = e - p * COUT;
-    gT[o * LDG + p] = p < np ? gb[(size_t)(p0 + p) * COUT + o] : (__bf16)0.f;
-  }
-  for (int e = tid; e < (kWP + TP - 1) * CIN; e += 256) {
-    const int j = e / CIN, c = e - j * CIN;
-    int pos = p0 - 2 + j;
-    pos %= M;
-    if (pos < 0) pos += M;
-    xT[c * LDI + j] = xb[(size_t)pos * CIN + c];
-  }
-  __syncthreads();
-  float* pw = part + (size_t)wg * COUT * TP * CIN;
-  for (int tile = wv; tile < NT; tile += 4) {
-    const int to = tile / TC, tc = tile - to * TC;
-    const int t = (tc * 16) / CIN, c0 = (tc * 16) - t * CIN;
-    f32x4 acc = {0, 0, 0, 0};
-#pragma unroll 2
+  const int wc = wv % WC, wo = (wv / WC) % WO, wt = wv / (WC * WO);
+  const int o0 = blockIdx.y * OH;
+  typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+  u32x4 gr[NGI][2], xr[NXI][2];
+  // item e: positions 2q, 2q + 1 of the chunk, channels 8 c8 .. (q = e % pairs:
+  // consecutive lanes store consecutive words)
+  auto fetch = [&](int ch) {
+    const int b = ch / cpr, p0 = (ch - b * cpr) * kWP;
+    const __bf16* gb = g + (size_t)b * M * COUT + o0;
+    const __bf16* xb = x + (size_t)b * M * CIN;
+#pragma unroll
+    for (int u = 0; u < NGI; ++u) {
+      const int e = u * 512 + tid, q = e % (kWP / 2), c8 = e / (kWP / 2);
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const int p = p0 + 2 * q + v;
+        gr[u][v] = u32x4{0, 0, 0, 0};
+        if (e < GI && p < M)
+          gr[u][v] = *reinterpret_cast<const u32x4*>(gb + (size_t)p * COUT + c8 * 8);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < NXI; ++u) {
+      const int e = u * 512 + tid, q = e % XP, c8 = e / XP;
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        int pos = p0 - 2 + 2 * q + v;
+        xr[u][v] = u32x4{0, 0, 0, 0};
+        if (e < XI) {
+          pos %= M;
+          if (pos < 0) pos += M;
+          xr[u][v] = *reinterpret_cast<const u32x4*>(xb + (size_t)pos * CIN + c8 * 8);
+        }
+      }
+    }
+  };
+  auto put = [&](__bf16* row0, int q, const u32x4 (&r)[2]) {
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+      const unsigned a = r[0][h], b = r[1][h];
+      *reinterpret_cast<unsigned*>(row0 + (2 * h) * LDP + 2 * q) = (a & 0xffffu) | (b << 16);
+      *reinterpret_cast<unsigned*>(row0 + (2 * h + 1) * LDP + 2 * q) = (a >> 16) | (b & 0xffff0000u);
+    }
+  };
+  double acc[TOW][NTW][4], bsum = 0.0;
+#pragma unroll
+  for (int z = 0; z < TOW; ++z)
+#pragma unroll
+    for (int t = 0; t < NTW; ++t)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[z][t][q] = 0.0;
+  int ch = blockIdx.x;
+  if (ch < nch) fetch(ch);
+  for (; ch < nch; ch += gridDim.x) {
+    __syncthreads();  // the previous chunk's reads are done
+#pragma unroll
+    for (int u = 0; u < NGI; ++u) {
+      const int e = u * 512 + tid, q = e % (kWP / 2), c8 = e / (kWP / 2);
+      if (e < GI) put(gT + c8 * 8 * LDP, q, gr[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < NXI; ++u) {
+      const int e = u * 512 + tid, q = e % XP, c8 = e / XP;
+      if (e < XI) put(xT + c8 * 8 * LDP, q, xr[u]);
+    }
+    __syncthreads();
+    if (ch + (int)gridDim.x < nch) fetch(ch + gridDim.x);
+    f32x4 fa[TOW][NTW];
+#pragma unroll
+    for (int z = 0; z < TOW; ++z)
+#pragma unroll
+      for (int t = 0; t < NTW; ++t) fa[z][t] = f32x4{0, 0, 0, 0};
+#pragma unroll
     for (int ks = 0; ks < kWP / 32; ++ks) {
       const int pk = ks * 32 + 8 * lg;
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(gT + (to * 16 + lr) * LDG + pk);
-      bf16x8 bb;
-      const __bf16* src = xT + (c0 + lr) * LDI + pk + t;
+      const __bf16* xrow = xT + (wc * 16 + lr) * LDP + pk;
+      const u32x4 wl = *reinterpret_cast<const u32x4*>(xrow);
+      const u32x4 wh = *reinterpret_cast<const u32x4*>(xrow + 8);
+      const unsigned w[8] = {wl[0], wl[1], wl[2], wl[3], wh[0], wh[1], wh[2], wh[3]};
+      bf16x8 a[TOW];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) bb[q] = src[q];
-      acc = mfma_bf16(a, bb, acc);
+      for (int z = 0; z < TOW; ++z)
+        a[z] = *reinterpret_cast<const bf16x8*>(gT + ((wo * TOW + z) * 16 + lr) * LDP + pk);
+      // the window of tap t: elements t .. t + 7 of the 16
+      auto tap = [&](auto tc, int i) {
+        constexpr int t = decltype(tc)::value;
+        u32x4 s;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          s[q] = (t & 1) ? __builtin_amdgcn_alignbit(w[t / 2 + q + 1], w[t / 2 + q], 16) : w[t / 2 + q];
+        const bf16x8 bb = __builtin_bit_cast(bf16x8, s);
+#pragma unroll
+        for (int z = 0; z < TOW; ++z) fa[z][i] = mfma_bf16(a[z], bb, fa[z][i]);
+      };
+      if constexpr (WT == 1) {
+        tap(std::integral_constant<int, 0>{}, 0);
+        tap(std::integral_constant<int, 1>{}, 1);
+        tap(std::integral_constant<int, 2>{}, 2);
+        tap(std::integral_constant<int, 3>{}, 3);
+        tap(std::integral_constant<int, 4>{}, 4);
+      } else if (wt == 0) {  // taps wt, wt + 2, ..
+        tap(std::integral_constant<int, 0>{}, 0);
+        tap(std::integral_constant<int, 2>{}, 1);
+        tap(std::integral_constant<int, 4>{}, 2);
+      } else {
+        tap(std::integral_constant<int, 1>{}, 0);
+        tap(std::integral_constant<int, 3>{}, 1);
+      }
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int o = to * 16 + 4 * lg + q;
-      pw[((size_t)o * TP + t) * CIN + c0 + lr] = acc[q];
+    for (int z = 0; z < TOW; ++z)
+#pragma unroll
+      for (int t = 0; t < NTW; ++t)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc[z][t][q] += (double)fa[z][t][q];
+    {
+      const int o = tid % OH, sub = tid / OH;
+      float s = 0.f;
+#pragma unroll
+      for (int p = 0; p < BP; ++p) s += (float)gT[o * LDP + sub * BP + p];
+      bsum += (double)s;
     }
   }
-  if (tid < COUT) {
-    float s = 0.f;
-    for (int p = 0; p < kWP; ++p) s += (float)gT[tid * LDG + p];
-    bpart[(size_t)wg * COUT + tid] = s;
+  double* pw = part + (size_t)blockIdx.x * COUT * 5 * CIN;
+#pragma unroll
+  for (int z = 0; z < TOW; ++z)
+#pragma unroll
+    for (int i = 0; i < NTW; ++i) {
+      const int t = wt + WT * i;
+      if (t >= 5) continue;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int o = o0 + (wo * TOW + z) * 16 + 4 * lg + q;
+        pw[((size_t)o * 5 + t) * CIN + wc * 16 + lr] = acc[z][i][q];
+      }
+    }
+  bs[tid] = bsum;
+  __syncthreads();
+  if (tid < OH) {
+    double s = 0.0;
+    for (int u = 0; u < BS; ++u) s += bs[u * OH + tid];
+    bpart[(size_t)blockIdx.x * COUT + o0 + tid] = s;
   }
 }
 
-// Sum of the partials in a fixed order into the FP32 gradient (oracle layout:
-// W[o][c][t] for the true sizes, then b[o]).
+// Sum of the ngrp partials in a fixed order into the FP32 gradient (oracle
+// layout: W[o][c][t] for the true sizes, then b[o]).  A workgroup takes 32
+// consecutive partial elements and eight threads each (coalesced 256-byte
+// reads): thread sub adds the groups sub, sub + 8, .. in order, then the
+// eight are added in order.
 template <int CIN, int COUT>
-__global__ void k_wgrad_reduce(int nwg, int cin, int cout, const float* part, const float* bpart,
-                               float* grad) {
-  constexpr int TP = taps_pad<CIN>();
-  const int nw = cout * cin * 5;
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < nw) {
-    const int o = e / (cin * 5), r = e - o * cin * 5, c = r / 5, t = r - c * 5;
-    double s = 0.0;
-    for (int w = 0; w < nwg; ++w) s += part[(((size_t)w * COUT + o) * TP + t) * CIN + c];
-    grad[e] = (float)s;
-  } else if (e < nw + cout) {
-    const int o = e - nw;
-    double s = 0.0;
-    for (int w = 0; w < nwg; ++w) s += bpart[(size_t)w * COUT + o];
-    grad[e] = (float)s;
+__global__ __launch_bounds__(256) void k_wgrad_reduce(int ngrp, int cin, int cout,
+                                                      const double* __restrict__ part,
+                                                      const double* __restrict__ bpart,
+                                                      float* grad) {
+  constexpr int NW = COUT * 5 * CIN;
+  __shared__ double red[8][32];
+  const int x = threadIdx.x & 31, sub = threadIdx.x >> 5, e = blockIdx.x * 32 + x;
+  double s = 0.0;
+  if (e < NW) {
+#pragma unroll 8
+    for (int w = sub; w < ngrp; w += 8) s += part[(size_t)w * NW + e];
+  } else if (e < NW + COUT) {
+#pragma unroll 8
+    for (int w = sub; w < ngrp; w += 8) s += bpart[(size_t)w * COUT + e - NW];
+  }
+  red[sub][x] = s;
+  __syncthreads();
+  if (sub != 0) return;
+  for (int u = 1; u < 8; ++u) s += red[u][x];
+  if (e < NW) {
+    const int o = e / (5 * CIN), r = e - o * 5 * CIN, t = r / CIN, c = r - t * CIN;
+    if (o < cout && c < cin) grad[((size_t)o * cin + c) * 5 + t] = (float)s;
+  } else if (e < NW + COUT && e - NW < cout) {
+    grad[(size_t)cout * cin * 5 + e - NW] = (float)s;
   }
 }
 
@@ -715,15 +850,17 @@ hipError_t conv(int B, int M, const __bf16* in, const __bf16* W, const float* bi
 }
 
 template <int CIN, int COUT>
-hipError_t wgrad(int B, int M, const __bf16* x, const __bf16* g, float* part, float* bpart,
+hipError_t wgrad(int B, int M, const __bf16* x, const __bf16* g, double* part, double* bpart,
                  int cin, int cout, float* grad, hipStream_t s) {
-  const int nx = (M + kWP - 1) / kWP;
-  hipLaunchKernelGGL((k_wgrad<CIN, COUT>), dim3(nx, B), dim3(256), 0, s, M, x, g, part, bpart);
+  constexpr int OH = CIN * COUT >= 4096 ? COUT / 2 : COUT;  // 64 -> 64: two channel slices
+  const int cpr = (M + kWP - 1) / kWP, nch = B * cpr;
+  const int most = OH < COUT ? kWgGroups64 : kWgGroups, ngrp = nch < most ? nch : most;
+  hipLaunchKernelGGL((k_wgrad<CIN, COUT, OH>), dim3(ngrp, COUT / OH), dim3(512), 0, s, M, nch, cpr,
+                     x, g, part, bpart);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const int tot = cout * cin * 5 + cout;
-  hipLaunchKernelGGL((k_wgrad_reduce<CIN, COUT>), dim3((tot + 255) / 256), dim3(256), 0, s,
-                     nx * B, cin, cout, part, bpart, grad);
+  hipLaunchKernelGGL((k_wgrad_reduce<CIN, COUT>), dim3((COUT * (5 * CIN + 1) + 31) / 32), dim3(256),
+                     0, s, ngrp, cin, cout, (const double*)part, (const double*)bpart, grad);
   return hipGetLastError();
 }
 
@@ -768,10 +905,12 @@ WsLayout wsnet_layout(int B, int M, int training) {
     L.g4 = take(2 * BM * 16);
     L.ga = take(2 * BM * 64);
     L.gb = take(2 * BM * 64);
-    const size_t nwg = (size_t)B * ((M + kWP - 1) / kWP);
-    L.nwg = (int)nwg;
-    L.part = take(4 * nwg * 64 * 6 * 64);
-    L.bpart = take(4 * nwg * 64);
+    const size_t nch = (size_t)B * ((M + kWP - 1) / kWP);
+    const size_t g64 = nch < (size_t)kWgGroups64 ? nch : (size_t)kWgGroups64;
+    const size_t g16 = nch < (size_t)kWgGroups ? nch : (size_t)kWgGroups;
+    const size_t b64 = 8 * g64 * 64 * 5 * 64, b16 = 8 * g16 * 64 * 5 * 16;
+    L.part = take(b64 > b16 ? b64 : b16);
+    L.bpart = take(8 * g16 * 64);
     L.grad = take(4 * wsnet_param_count());
     L.lpart = take(8 * (size_t)B);
   }
@@ -826,8 +965,8 @@ hipError_t wsnet_loss_grad(int B, int M, const float* params, const float* feat,
   if ((e = hipGetLastError()) != hipSuccess) return e;
   auto A = [&](int l) { return (const __bf16*)(ws + L.act[l]); };
   auto Wb = [&](int l) { return (const __bf16*)(ws + L.Wb[l]); };
-  float* part = (float*)(ws + L.part);
-  float* bpart = (float*)(ws + L.bpart);
+  double* part = (double*)(ws + L.part);
+  double* bpart = (double*)(ws + L.bpart);
   __bf16* ga = (__bf16*)(ws + L.ga);
   __bf16* gb = (__bf16*)(ws + L.gb);
   auto G = [&](int l) { return grad + wsnet_param_offset(l); };

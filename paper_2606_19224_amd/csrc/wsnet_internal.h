@@ -14,7 +14,6 @@ struct WsLayout {
   size_t act[4], out;             // activations (BF16), network output (FP32)
   size_t g4, ga, gb;              // gradients in the activations (training)
   size_t part, bpart, grad, lpart;
-  int nwg;                        // weight-gradient workgroups
   size_t total;
 };
 
