@@ -536,6 +536,7 @@ TriBuffers<T> tri_buffers(const Layout& L, void* ws, bool warm) {
   t.yp = (T*)(b + L.ty);
   t.rp = (T*)(b + L.tr);
   t.zt = warm ? (T*)(b + L.tzt) : nullptr;
+  t.pend = (double*)(b + L.tzt);
   t.err = (int*)(b + L.terr);
   return t;
 }

@@ -276,6 +276,7 @@ struct TriBuffers {
   T* yp;           // m, y' = 0
   T* rp;           // m, R' = I
   T* zt;           // m x N, L^T z0 (warm start) or null
+  double* pend;    // chunk products of the substitution (zt's region, before zt is written)
   int* err;        // index error of the whitening pass (bit 1)
 };
 template <typename T>
