@@ -74,13 +74,6 @@ int resident_pad(int N, int prec) {
   return 0;  // resident solver not available: streaming only
 }
 
-int reduced_rows(int N) {
-  long r = (long)((48 * 1024) / (2 * 8 * (size_t)N + 16));
-  if (r > 128) r = 128;
-  if (r < 1) r = 1;
-  return (int)r;
-}
-
 }  // namespace
 
 // The precisions the library knows; the float-data ones the row-block x
@@ -196,11 +189,15 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       L.rWt = take(esz * (size_t)np * np);
       L.rerr = take(sizeof(int) * (size_t)mpad);  // one word per gather workgroup
     } else {
-      L.RB = reduced_rows(N);
-      L.nblk = (m + L.RB - 1) / L.RB;
-      L.nwg_max = L.nblk < kMaxGrid ? L.nblk : kMaxGrid;
-      L.rpart = take(sizeof(double) * 2 * NN * L.nwg_max);
-      L.rG = take(sizeof(double) * NN);
+      // N > 128: FP64 whatever prec is; G padded to 192 or 256 for the on-chip
+      // CG, N x N above
+      reduced_wide_shape(m, N, &L.rWNP, &L.rmpad, &L.rKC, &L.rS);
+      const size_t wp = (size_t)L.rWNP;
+      L.rLG = N <= 256 ? L.rWNP : N;
+      L.rQ = take(sizeof(double) * (size_t)L.rmpad * 2 * wp);
+      L.rpart = take(sizeof(double) * (size_t)L.rS * wp * 2 * wp);
+      L.rG = take(sizeof(double) * (size_t)L.rLG * L.rLG);
+      L.rerr = take(sizeof(int) * (size_t)L.rmpad);
     }
     L.rB = take(sizeof(double) * NN);
     L.Wd = take(sizeof(double) * NN);

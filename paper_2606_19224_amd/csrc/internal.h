@@ -151,12 +151,12 @@ struct Layout {
   int gv;
   size_t xflags, pend, err;
   int NP;  // partial/Gram stride: max(N, resident padding of N)
-  // reduced mode (rNP != 0: the MFMA path, with Q = [P | Yt] at rQ and
-  // (W - I)^T at rWt; otherwise the scalar path for N > 128)
+  // reduced mode (rNP != 0: N <= 128, with Q = [P | Yt] at rQ and (W - I)^T at
+  // rWt; otherwise N > 128 padded to rWNP, G of stride rLG)
   size_t rpart, rG, rB, riters, rstat, rQ, rWt, rerr;
   // non-diagonal R (mode bit 2): whitening scratch and substitute inputs
   size_t tSd, tDd, tXp, tEp, tidx, tw, ty, tr, tzt, terr;
-  int rNP, rmpad, rKC, rS;
+  int rNP, rmpad, rKC, rS, rWNP, rLG;
   // row-block x member-group solver (FP32): its exchange words (0 if not
   // applicable) and shape
   size_t tx, tS, tR;
@@ -251,6 +251,8 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
 // 64 or 128), m padded to mpad (a multiple of 32), KC rows per chunk of the
 // N x 2N product and S chunks.  0 when N is out of range.
 int reduced_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
+// The same for N > 128: NP a multiple of 64, mpad, KC and S as above.
+void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
 // Xg (ng rows) is the array the observations are gathered from; Xf is
 // updated (the same unless R is not diagonal)
 template <typename T>

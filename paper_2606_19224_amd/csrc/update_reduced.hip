@@ -46,6 +46,107 @@ __global__ __launch_bounds__(kBlock) void k_update(int n, int N, int RBX, const 
   }
 }
 
+// The same update for ensembles past the tiled kernels' widths (N > 128 in
+// FP32, 64 in FP64): FP64 products on the 16x16x4 MFMA whatever T is.  A
+// workgroup owns 16 RT whole rows of X_f, kept in LDS in T (so X_a may alias
+// X_f), and its waves take 16-column tiles of W in turn; W comes from L2
+// straight into the MFMA's B operand (16 lanes read 128 consecutive bytes)
+// one step of four ahead.  Lane group lk sums the run lk KQ .. lk KQ + KQ - 1
+// of the summation index.  Bound: FP64 MFMA, 2 n N^2 flops padded to 16
+// (n = 20011, N = 200: one double FMA chain per element took 370 us).
+template <typename T, int RT>
+__global__ __launch_bounds__(kBlock) void k_update_wide(int n, int N, const T* Xf, T* Xa,
+                                                        const double* Wd, int mode,
+                                                        const int* skip) {
+  constexpr int RB = 16 * RT, PAD = 16 / (int)sizeof(T);
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  if (skip && (*skip & 4)) return;
+  const int TJ = (N + 15) / 16, KQ = 4 * TJ, LD = 16 * TJ + PAD;
+  T* As = (T*)smem_raw;  // RB x LD, zero past n and N
+  __shared__ double mean[RB];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lk = lane >> 4;
+  const int i0 = blockIdx.x * RB, rows = min(RB, n - i0);
+  for (int r = wv; r < RB; r += kBlock / 64)
+    for (int c = lane; c < 16 * TJ; c += 64)
+      As[r * LD + c] = (r < rows && c < N) ? Xf[(size_t)(i0 + r) * N + c] : (T)0;
+  __syncthreads();
+  for (int r = tid / 8; r < RB; r += kBlock / 8) {
+    const int q = tid % 8;
+    double sum = 0.0;
+    if (mode == 0)
+      for (int c = q; c < N; c += 8) sum += (double)As[r * LD + c];
+    sum = group_sum<8>(sum);
+    if (q == 0) mean[r] = sum / N;
+  }
+  __syncthreads();
+  double mu[RT];
+#pragma unroll
+  for (int z = 0; z < RT; ++z) mu[z] = mean[16 * z + lr];
+  for (int tj = wv; tj < TJ; tj += kBlock / 64) {
+    const int col = tj * 16 + lr;
+    const bool cv = col < N;
+    const double* wcol = Wd + (size_t)(lk * KQ) * N + (cv ? col : 0);
+    v4d acc[RT];
+#pragma unroll
+    for (int z = 0; z < RT; ++z) acc[z] = v4d{0.0, 0.0, 0.0, 0.0};
+    double bn[4];
+    auto fetch = [&](int t0) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        bn[t] = (cv && lk * KQ + t0 + t < N) ? wcol[(size_t)(t0 + t) * N] : 0.0;
+    };
+    fetch(0);
+    for (int t0 = 0; t0 < KQ; t0 += 4) {
+      double bc[4];
+#pragma unroll
+      for (int t = 0; t < 4; ++t) bc[t] = bn[t];
+      if (t0 + 4 < KQ) fetch(t0 + 4);
+      double av[RT][4];
+#pragma unroll
+      for (int z = 0; z < RT; ++z) {
+        load4d(As + (16 * z + lr) * LD + lk * KQ + t0, av[z]);
+        // columns past N meet zero rows of W; past n the result is dropped
+#pragma unroll
+        for (int t = 0; t < 4; ++t) av[z][t] -= mu[z];
+      }
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int z = 0; z < RT; ++z) acc[z] = mfma4(av[z][t], bc[t], acc[z]);
+    }
+#pragma unroll
+    for (int z = 0; z < RT; ++z)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * z + frag_row<double>(lk, i);
+        if (r < rows && cv) {
+          double v = acc[z][i];
+          if (mode == 0) v += (double)As[r * LD + col];
+          Xa[(size_t)(i0 + r) * N + col] = (T)v;
+        }
+      }
+  }
+}
+
+// LDS of a k_update_wide workgroup, and the launch (false: it does not fit).
+template <typename T>
+size_t update_wide_lds(int N, int RT) {
+  return sizeof(T) * (size_t)(16 * RT) * (((N + 15) / 16) * 16 + 16 / sizeof(T));
+}
+constexpr size_t kUpdWideLds = 128 * 1024;
+
+template <typename T, int RT>
+hipError_t launch_update_wide(int n, int N, const T* Xf, T* Xa, const double* Wd, int mode,
+                              const int* skip, hipStream_t s) {
+  const size_t lds = update_wide_lds<T>(N, RT);
+  const hipError_t e = hipFuncSetAttribute((const void*)k_update_wide<T, RT>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_update_wide<T, RT>), dim3((n + 16 * RT - 1) / (16 * RT)), dim3(kBlock),
+                     lds, s, n, N, Xf, Xa, Wd, mode, skip);
+  return hipGetLastError();
+}
+
 // The same update on the 16x16x4 MFMA for N <= 128 (FP32) or N <= 64 (FP64),
 // 64-row tiles (see update_tile.h): each workgroup brings W into LDS once
 // and then takes every gridDim.x-th tile.
@@ -225,91 +326,6 @@ hipError_t launch_update_mfma(int n, int N, const T* Xf, T* Xa, const double* Wd
   return hipGetLastError();
 }
 
-// Reduced mode, step 1 (Algorithm 2 setup, Table 2 "N x N matrix form"):
-// per row block, HX, zbar, P = (HX - zbar 1^T)/l_i and Yt = ((y - zbar) 1^T + E)/l_i
-// with l_i = sqrt((N-1) r_i); partial [P^T P | P^T Yt] (N x 2N) per workgroup.
-// SEN (the sEnKF of Appendix A, Algorithm 3): l_i^2 = ||s_i||^2 + (N-1) r_i,
-// the i-th diagonal entry of Zhat Zhat^T + (N-1) R, and Yt = (Y - HX)/l_i, so
-// that the right half is Zhat^T diag(Zhat Zhat^T + (N-1) R)^{-1} (Y - Z); the
-// left half is not formed.
-template <typename T, bool SEN>
-__global__ __launch_bounds__(kBlock) void k_red_gram(int n, int m, int N, int k, int RB, int nblk,
-                                                     const T* Xf, const int32_t* idx,
-                                                     const T* hw, const T* y, const T* rdiag,
-                                                     const T* eps, double* part, int* err) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  double* lp = (double*)smem_raw;           // RB * N
-  double* ly = lp + (size_t)RB * N;         // RB * N
-  double* lz = ly + (size_t)RB * N;         // RB: zbar_i
-  double* ll = lz + RB;                     // RB: l_i
-  const int tid = threadIdx.x, wg = blockIdx.x, nwg = gridDim.x;
-  double* out = part + (size_t)wg * 2 * N * N;
-  for (int b = wg; b < nblk; b += nwg) {
-    const bool first = (b == wg);
-    const int i0 = b * RB, rows = min(RB, m - i0), ne = rows * N;
-    for (int e = tid; e < ne; e += kBlock) {
-      const int i = e / N, j = e - i * N, gi = i0 + i;
-      double h = 0;
-      for (int t = 0; t < k; ++t) {
-        const int c = idx[(size_t)gi * k + t];
-        if ((unsigned)c < (unsigned)n)
-          h += (double)hw[(size_t)gi * k + t] * (double)Xf[(size_t)c * N + j];
-        else
-          atomicOr(err, 2);
-      }
-      lp[e] = h;
-    }
-    __syncthreads();
-    for (int i = tid; i < rows; i += kBlock) {
-      double s = 0;
-      for (int j = 0; j < N; ++j) s += lp[i * N + j];
-      const double zb = s / N;
-      double l2 = (double)(N - 1) * (double)rdiag[i0 + i];
-      if constexpr (SEN) {
-        double ss = 0;
-        for (int j = 0; j < N; ++j) ss += (lp[i * N + j] - zb) * (lp[i * N + j] - zb);
-        l2 += ss;
-      }
-      lz[i] = zb;
-      ll[i] = sqrt(l2);
-    }
-    __syncthreads();
-    for (int e = tid; e < ne; e += kBlock) {
-      const int i = e / N, gi = i0 + i;
-      const double l = ll[i];
-      const double zb = lz[i];
-      double yt = (double)y[gi] - (SEN ? lp[e] : zb);
-      if (eps) yt += (double)eps[(size_t)i0 * N + e];
-      lp[e] = (lp[e] - zb) / l;
-      ly[e] = yt / l;
-    }
-    __syncthreads();
-    for (int o = tid + (SEN ? N * N : 0); o < 2 * N * N; o += kBlock) {
-      const int half = o / (N * N), oo = o - half * N * N;
-      const int kk = oo / N, j = oo - kk * N;
-      const double* v = half ? ly : lp;
-      double acc = 0;
-      for (int i = 0; i < rows; ++i) acc += lp[i * N + kk] * v[i * N + j];
-      out[o] = first ? acc : out[o] + acc;
-    }
-    __syncthreads();
-  }
-}
-
-// G = I + sum_w P^T P,  B = I + sum_w P^T Yt  (fixed summation order).
-// o0 = N * N forms B only; dadd is the diagonal added (1, or 0 for the sEnKF).
-__global__ __launch_bounds__(kBlock) void k_red_sum(int N, int nwg, const double* part, double* G,
-                                                    double* B, int o0, double dadd) {
-  const int o = o0 + blockIdx.x * kBlock + threadIdx.x;
-  if (o >= 2 * N * N) return;
-  double acc = 0;
-  for (int w = 0; w < nwg; ++w) acc += part[(size_t)w * 2 * N * N + o];
-  const int half = o / (N * N), oo = o - half * N * N;
-  const int kk = oo / N, j = oo - kk * N;
-  acc += (kk == j) ? dadd : 0.0;
-  (half ? B : G)[oo] = acc;
-}
-
 __device__ inline double bsum(double v, double* red) {
   const int tid = threadIdx.x;
   __syncthreads();
@@ -338,8 +354,8 @@ __device__ inline int small_cg_status(bool nonfinite, double rho, double thr) {
 // exact arithmetic).  Vectors live in LDS; G is read from L2 (symmetric, so
 // q_k = sum_l G[l][k] p_l reads rows coalesced).
 __global__ __launch_bounds__(kBlock) void k_small_cg(int N, const double* G, const double* B,
-                                                     double* W, int* iters, int* status,
-                                                     double tol, int maxit) {
+                                                     double* W, int* iters, int* iters2,
+                                                     int* status, double tol, int maxit) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* x = (double*)smem_raw;
   double* r = x + N;
@@ -389,6 +405,7 @@ __global__ __launch_bounds__(kBlock) void k_small_cg(int N, const double* G, con
   for (int kk = tid; kk < N; kk += kBlock) W[(size_t)kk * N + j] = x[kk];
   if (tid == 0) {
     iters[j] = it;
+    if (iters2) iters2[j] = it;
     status[j] = small_cg_status(nonfinite, rho, thr);
   }
 }
@@ -939,6 +956,320 @@ __global__ __launch_bounds__(kBlock) void k_red_update(int n, int N, const T* Xf
   update_tiles_stream<T, NP, kBlock, RB>(n, N, Xf, Xa, 1, As, As, Wt, mean);
 }
 
+// ---------------------------------------------------------------------------
+// Reduced mode and sEnKF for N > 128, in FP64 whatever T is: NP = N rounded up
+// to 64, Q (mpad x 2NP, as above, in double) through memory, the product on
+// the FP64 MFMA in 64 x 64 tiles over row chunks.  (One workgroup per row
+// block with a scalar FP64 sum per output, and a serial sum over up to 1024
+// N x 2N parts, took 277 + 88 us at m = 5003, N = 200.)
+// ---------------------------------------------------------------------------
+
+// Row i of Q, one wave per row.  HX is kept in the row's left half until its
+// mean is known.  errw and SEN as in k_red_prep.
+template <typename T, bool SEN>
+__global__ __launch_bounds__(kBlock) void k_red_prep_wide(int n, int m, int N, int NP, int k,
+                                                          const T* Xf, const int32_t* idx,
+                                                          const T* hw, const T* y, const T* rdiag,
+                                                          const T* eps, double* Q, int* errw) {
+  __shared__ int bad;
+  const int lane = threadIdx.x & 63, i = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (threadIdx.x == 0) bad = 0;
+  __syncthreads();
+  double* qr = Q + (size_t)i * 2 * NP;
+  const bool live = i < m;
+  constexpr int U = 4;
+  double sum = 0.0;
+  for (int j0 = lane; j0 < NP; j0 += 64 * U) {
+    double h[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) h[u] = 0.0;
+    if (live)
+      for (int t = 0; t < k; ++t) {
+        const int c = idx[(size_t)i * k + t];
+        if ((unsigned)c >= (unsigned)n) {
+          if (lane == 0) atomicOr(&bad, 2);
+          continue;
+        }
+        const double w = (double)hw[(size_t)i * k + t];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+          if (j0 + 64 * u < N) h[u] += w * (double)Xf[(size_t)c * N + j0 + 64 * u];
+      }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (j0 + 64 * u < NP) {
+        qr[j0 + 64 * u] = h[u];
+        sum += h[u];
+      }
+  }
+  const double zb = wave_sum(sum) / N;
+  double l2 = live ? (double)(N - 1) * (double)rdiag[i] : 1.0;
+  if constexpr (SEN) {
+    double ss = 0.0;
+    for (int j = lane; j < N; j += 64) ss += (qr[j] - zb) * (qr[j] - zb);
+    l2 += wave_sum(ss);
+  }
+  const double l = sqrt(l2), yv = live ? (double)y[i] : 0.0;
+  for (int j = lane; j < NP; j += 64) {
+    const bool on = live && j < N;
+    const double h = qr[j];
+    double yt = yv - (SEN ? h : zb);
+    if (on && eps) yt += (double)eps[(size_t)i * N + j];
+    qr[j] = on ? (h - zb) / l : 0.0;
+    qr[NP + j] = on ? yt / l : 0.0;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) errw[blockIdx.x] = bad;
+}
+
+// part[s] = Q[rows of chunk s, :NP]^T Q[rows of chunk s, :], tiles t0 .. of
+// the tile list of k_red_gemm.  All tiles of a chunk run on one XCD
+// (workgroup w runs on XCD w mod 8), whose L2 then serves the chunk's rows to
+// every tile after the first.
+__global__ __launch_bounds__(kBlock) void k_red_gemm_wide(int NP, int KC, int mpad, int S, int t0,
+                                                          int ntile, const double* Q,
+                                                          double* part) {
+  constexpr int MB = 2, HS = 32;
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
+  const int TT = NP / 64, NTG = TT * (TT + 1) / 2, slot = blockIdx.x / 8;
+  const int chunk = (int)(blockIdx.x % 8) + 8 * (slot / ntile);
+  if (chunk >= S) return;
+  int t = t0 + slot % ntile, ta = 0, tb;
+  if (t < NTG) {
+    while (t >= TT - ta) t -= TT - ta++;
+    tb = ta + t;
+  } else {
+    t -= NTG;
+    ta = t / TT;
+    tb = TT + t % TT;
+  }
+  const int ca = ta * 64 + (wv >> 1) * HS + lr, cb = tb * 64 + (wv & 1) * HS + lr;
+  const int r0 = chunk * KC, r1 = min(mpad, r0 + KC);
+  const size_t QW = 2 * (size_t)NP;
+  v4d acc[MB][MB];
+#pragma unroll
+  for (int x = 0; x < MB; ++x)
+#pragma unroll
+    for (int z = 0; z < MB; ++z) acc[x][z] = v4d{0.0, 0.0, 0.0, 0.0};
+  double an[4][MB], bn[4][MB];
+  auto load = [&](int r) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const double* row = Q + (size_t)(r + 4 * u + lk) * QW;
+#pragma unroll
+      for (int x = 0; x < MB; ++x) {
+        an[u][x] = row[ca + 16 * x];
+        bn[u][x] = row[cb + 16 * x];
+      }
+    }
+  };
+  load(r0);
+  for (int r = r0; r < r1; r += 16) {
+    double ac[4][MB], bc[4][MB];
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int x = 0; x < MB; ++x) {
+        ac[u][x] = an[u][x];
+        bc[u][x] = bn[u][x];
+      }
+    if (r + 16 < r1) load(r + 16);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int x = 0; x < MB; ++x)
+#pragma unroll
+        for (int z = 0; z < MB; ++z) acc[x][z] = mfma4(ac[u][x], bc[u][z], acc[x][z]);
+  }
+  double* out = part + (size_t)chunk * NP * QW;
+#pragma unroll
+  for (int x = 0; x < MB; ++x)
+#pragma unroll
+    for (int z = 0; z < MB; ++z)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        out[(size_t)(ca - lr + 16 * x + frag_row<double>(lk, i)) * QW + cb + 16 * z] = acc[x][z][i];
+}
+
+// G = I + sum_s part_s[:, :NP] (from its upper tiles; stride LG, rows and
+// columns < LG) and B = dadd I + sum_s part_s[:, NP:] (N x N), parts in order.
+// left = 0: B only.  Workgroup 0 folds the gather's error words into err.
+__global__ __launch_bounds__(kBlock) void k_red_sum_wide(int N, int NP, int LG, int S, int left,
+                                                         double dadd, const double* part,
+                                                         double* G, double* B, const int* errw,
+                                                         int nerr, int* err) {
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0) {
+    __shared__ int flags;
+    if (tid == 0) flags = 0;
+    __syncthreads();
+    int f = 0;
+    for (int e = tid; e < nerr; e += kBlock) f |= errw[e];
+    if (f) atomicOr(&flags, f);
+    __syncthreads();
+    if (tid == 0) *err = flags;
+  }
+  const int W = left ? 2 * NP : NP, o = blockIdx.x * kBlock + tid;
+  if (o >= NP * W) return;
+  const int a = o / W, b = o - a * W + (left ? 0 : NP);
+  const bool right = b >= NP;
+  const int bb = right ? b - NP : b;
+  if (right ? (a >= N || bb >= N) : (a / 64 > bb / 64)) return;
+  const size_t stride = (size_t)NP * 2 * NP;
+  const double* src = part + (size_t)a * 2 * NP + b;
+  double acc = 0.0;
+#pragma unroll 8
+  for (int s = 0; s < S; ++s) acc += src[s * stride];
+  if (right) {
+    B[(size_t)a * N + bb] = acc + (a == bb ? dadd : 0.0);
+  } else if (a < LG && bb < LG) {
+    if (a == bb && a < N) acc += 1.0;
+    G[(size_t)a * LG + bb] = acc;
+    if (a / 64 < bb / 64) G[(size_t)bb * LG + a] = acc;
+  }
+}
+
+// The column CG of k_small_cg for 128 < N <= 256 with G on chip (LG = 64 RPL
+// rows of stride LG, zero outside N x N): eight waves, each with LG/8 rows of
+// G, RR of them in registers and the rest in LDS, since 512 KiB of G at LG =
+// 256 fit neither alone.  Every wave carries the whole recurrence and forms
+// its rows' part of q = G p (see k_small_cg_w); the eight parts meet in LDS.
+// Reading G from L2 every step took 378 us for 200 columns.
+template <int RPL>
+struct SmallCgX {
+  static constexpr int LG = 64 * RPL, NW = 8, QR = LG / NW, RR = 24, RL = QR - RR;
+  static constexpr size_t lds = sizeof(double) * ((size_t)NW * RL * LG + NW * LG + NW * QR + LG);
+};
+template <int RPL>
+__global__ __launch_bounds__(512) void k_small_cg_x(int N, const double* Gp, const double* B,
+                                                    double* W, int* iters, int* iters2,
+                                                    int* status, double tol, int maxit) {
+  using C = SmallCgX<RPL>;
+  constexpr int LG = C::LG, NW = C::NW, QR = C::QR, RR = C::RR, RL = C::RL;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  double* gl = (double*)smem_raw;         // NW x RL x LG
+  double* qp = gl + (size_t)NW * RL * LG; // NW x LG
+  double* ps = qp + NW * LG;              // NW x QR
+  double* xs = ps + NW * QR;              // LG: the iterate, kept by wave 0 (registers are short)
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, j = blockIdx.x;
+  const int l0 = wv * QR;
+  double gr[RR][RPL];
+#pragma unroll
+  for (int t = 0; t < RR; ++t)
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) gr[t][u] = Gp[(size_t)(l0 + t) * LG + lane + 64 * u];
+  double* myg = gl + (size_t)wv * RL * LG;
+#pragma unroll
+  for (int t = 0; t < RL; ++t)
+#pragma unroll
+    for (int u = 0; u < RPL; ++u)
+      myg[t * LG + lane + 64 * u] = Gp[(size_t)(l0 + RR + t) * LG + lane + 64 * u];
+  double r[RPL], p[RPL];
+  double part = 0.0;
+#pragma unroll
+  for (int u = 0; u < RPL; ++u) {
+    const int i = lane + 64 * u;
+    const double b = i < N ? B[(size_t)i * N + j] : 0.0;
+    if (wv == 0) xs[i] = 0.0;
+    r[u] = b;
+    p[u] = b;
+    part += b * b;
+  }
+  double rho = wave_sum(part);
+  const double thr = tol * sqrt(rho);
+  double* myp = ps + wv * QR;
+  int it = 0;
+  bool nonfinite = false;
+  while (sqrt(rho) > thr && it < maxit && rho > 0.0) {
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) {
+      const int i = lane + 64 * u - l0;
+      if (i >= 0 && i < QR) myp[i] = p[u];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    double qa[RPL];
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) qa[u] = 0.0;
+#pragma unroll
+    for (int t = 0; t < QR; t += 2) {
+      const v2d pv = *reinterpret_cast<const v2d*>(myp + t);
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+#pragma unroll
+        for (int u = 0; u < RPL; ++u) {
+          double g;
+          if constexpr (RL > 0) {
+            g = t + c < RR ? gr[t + c < RR ? t + c : 0][u]
+                           : myg[(t + c - RR) * LG + lane + 64 * u];
+          } else {
+            g = gr[t + c][u];
+          }
+          qa[u] += g * pv[c];
+        }
+    }
+    __syncthreads();  // the previous step's sums are read
+    double* qw = qp + (size_t)wv * LG;
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) qw[lane + 64 * u] = qa[u];
+    __syncthreads();
+    double q[RPL];
+    part = 0.0;
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) {
+      const double* qb = qp + lane + 64 * u;
+      double v = qb[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) v += qb[(size_t)w * LG];
+      q[u] = v;
+      part += p[u] * v;
+    }
+    const double alpha = rho / wave_sum(part);
+    part = 0.0;
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) {
+      if (wv == 0) xs[lane + 64 * u] += alpha * p[u];
+      r[u] -= alpha * q[u];
+      part += r[u] * r[u];
+    }
+    const double rho_new = wave_sum(part);
+    const double beta = rho_new / rho;
+#pragma unroll
+    for (int u = 0; u < RPL; ++u) p[u] = r[u] + beta * p[u];
+    rho = rho_new;
+    ++it;
+    // the same bits in every lane and wave, so the exit is uniform
+    if (!isfinite(alpha) || !isfinite(beta)) {
+      nonfinite = true;
+      break;
+    }
+  }
+  if (wv != 0) return;
+#pragma unroll
+  for (int u = 0; u < RPL; ++u) {
+    const int i = lane + 64 * u;
+    if (i < N) W[(size_t)i * N + j] = xs[i];
+  }
+  if (lane == 0) {
+    iters[j] = it;
+    if (iters2) iters2[j] = it;
+    status[j] = small_cg_status(nonfinite, rho, thr);
+  }
+}
+
+template <int RPL>
+hipError_t launch_small_cg_x(int N, const double* G, const double* B, double* W, int* iters,
+                             int* iters2, int* status, double tol, int maxit, hipStream_t s) {
+  constexpr size_t lds = SmallCgX<RPL>::lds;
+  const hipError_t e = hipFuncSetAttribute((const void*)k_small_cg_x<RPL>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_small_cg_x<RPL>, dim3(N), dim3(512), lds, s, N, G, B, W, iters, iters2,
+                     status, tol, maxit);
+  return hipGetLastError();
+}
+
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_validate(int n, int m, int N, int k, const T* Xf,
                                                      const int32_t* idx, const T* hw, const T* y,
@@ -990,7 +1321,12 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
   if (N <= 64) return launch_update_mfma<T, 64>(n, N, Xf, Xa, Wd, mode, skip, s);
   if constexpr (sizeof(T) == 4)
     if (N <= 128) return launch_update_mfma<T, 128>(n, N, Xf, Xa, Wd, mode, skip, s);
-  // larger ensembles: one double FMA chain per element
+  // larger ensembles: 32 rows a workgroup while they fit its LDS, else 16, else
+  // (N past 2000 in FP32, 1000 in FP64) one double FMA chain per element
+  if (update_wide_lds<T>(N, 2) <= kUpdWideLds)
+    return launch_update_wide<T, 2>(n, N, Xf, Xa, Wd, mode, skip, s);
+  if (update_wide_lds<T>(N, 1) <= kUpdWideLds)
+    return launch_update_wide<T, 1>(n, N, Xf, Xa, Wd, mode, skip, s);
   const int RBX = update_rows(N);
   const size_t sh = sizeof(double) * ((size_t)RBX * N + RBX);
   hipLaunchKernelGGL(k_update<T>, dim3((n + RBX - 1) / RBX), dim3(kBlock), sh, s, n, N, RBX, Xf,
@@ -1022,6 +1358,22 @@ int reduced_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
   *KC = (int)kc;
   *S = (int)((mp + kc - 1) / kc);
   return 1;
+}
+
+void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
+  const int np = (N + 63) / 64 * 64, TT = np / 64, tiles = TT * (TT + 1) / 2 + TT * TT;
+  const long mp = ((long)m + 31) / 32 * 32, blocks = mp / 32;
+  // about 512 workgroups, in whole rounds over the eight XCDs, chunks of at
+  // least 64 rows
+  long sc = (512 / tiles + 7) / 8 * 8;
+  const long smax = (mp + 63) / 64;
+  if (sc > smax) sc = smax;
+  if (sc < 1) sc = 1;
+  const long kc = (blocks + sc - 1) / sc * 32;
+  *NP = np;
+  *mpad = (int)mp;
+  *KC = (int)kc;
+  *S = (int)((mp + kc - 1) / kc);
 }
 
 namespace {
@@ -1129,6 +1481,34 @@ hipError_t launch_reduced_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, c
 
 }  // namespace
 
+namespace {
+// N > 128: Q, its product's parts and their sums (G and B; B only for SEN).
+template <typename T, bool SEN>
+hipError_t red_wide_product(int ng, int m, int N, int k, const T* Xg, const int32_t* idx,
+                            const T* hw, const T* y, const T* rdiag, const T* eps, void* ws,
+                            const Layout& L, hipStream_t s) {
+  unsigned char* base = (unsigned char*)ws;
+  double* Q = (double*)(base + L.rQ);
+  double* part = (double*)(base + L.rpart);
+  int* errw = (int*)(base + L.rerr);
+  const int NP = L.rWNP, nprep = L.rmpad / (kBlock / 64), TT = NP / 64, NTG = TT * (TT + 1) / 2;
+  hipLaunchKernelGGL((k_red_prep_wide<T, SEN>), dim3(nprep), dim3(kBlock), 0, s, ng, m, N, NP, k,
+                     Xg, idx, hw, y, rdiag, eps, Q, errw);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int t0 = SEN ? NTG : 0, ntile = NTG + TT * TT - t0;
+  hipLaunchKernelGGL(k_red_gemm_wide, dim3(8 * ntile * ((L.rS + 7) / 8)), dim3(kBlock), 0, s, NP,
+                     L.rKC, L.rmpad, L.rS, t0, ntile, (const double*)Q, part);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const int W = SEN ? NP : 2 * NP;
+  hipLaunchKernelGGL(k_red_sum_wide, dim3((NP * W + kBlock - 1) / kBlock), dim3(kBlock), 0, s, N,
+                     NP, L.rLG, L.rS, SEN ? 0 : 1, SEN ? 0.0 : 1.0, (const double*)part,
+                     (double*)(base + L.rG), (double*)(base + L.rB), (const int*)errw, nprep,
+                     (int*)(base + L.err));
+  return hipGetLastError();
+}
+}  // namespace
+
 template <typename T>
 hipError_t launch_reduced(int n, int m, int N, int k, const T* Xf, T* Xa, const T* Xg, int ng,
                           const int32_t* idx, const T* hw, const T* y, const T* rdiag,
@@ -1143,33 +1523,25 @@ hipError_t launch_reduced(int n, int m, int N, int k, const T* Xf, T* Xa, const 
   if (L.rNP == 128)
     return launch_reduced_mfma<T, 128>(n, m, N, k, Xf, Xa, Xg, ng, idx, hw, y, rdiag, eps, tol, maxit,
                                        ws, L, iters_out, s);
-  // N > 128: one workgroup per row block with scalar FP64 sums, then the
-  // workgroup-per-column solve
   unsigned char* base = (unsigned char*)ws;
-  double* part = (double*)(base + L.rpart);
   double* G = (double*)(base + L.rG);
   double* B = (double*)(base + L.rB);
   double* Wd = (double*)(base + L.Wd);
-  int* iters = iters_out ? iters_out : (int*)(base + L.riters);
-  const int nwg = L.nwg_max;
-  const size_t sh = sizeof(double) * (2 * (size_t)L.RB * N + 2 * L.RB);
-  int* err = (int*)(base + L.err);
-  hipError_t e = launch_zero_u32((unsigned*)err, 1, s);
+  int* iters = (int*)(base + L.riters);
+  int* stat = (int*)(base + L.rstat);
+  hipError_t e = red_wide_product<T, false>(ng, m, N, k, Xg, idx, hw, y, rdiag, eps, ws, L, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_red_gram<T, false>), dim3(nwg), dim3(kBlock), sh, s, ng, m, N, k, L.RB,
-                     L.nblk, Xg, idx, hw, y, rdiag, eps, part, err);
-  e = hipGetLastError();
+  if (L.rLG == 192) {
+    e = launch_small_cg_x<3>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s);
+  } else if (L.rLG == 256) {
+    e = launch_small_cg_x<4>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s);
+  } else {  // N > 256: G no longer fits a CU
+    hipLaunchKernelGGL(k_small_cg, dim3(N), dim3(kBlock),
+                       sizeof(double) * (4 * (size_t)N + kBlock), s, N, (const double*)G,
+                       (const double*)B, Wd, iters, iters_out, stat, tol, maxit);
+    e = hipGetLastError();
+  }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_red_sum, dim3((2 * N * N + kBlock - 1) / kBlock), dim3(kBlock), 0, s, N,
-                     nwg, part, G, B, 0, 1.0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_small_cg, dim3(N), dim3(kBlock), sizeof(double) * (4 * (size_t)N + kBlock),
-                     s, N, G, B, Wd, iters, (int*)(base + L.rstat), tol, maxit);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (iters != (int*)(base + L.riters))
-    if ((e = hipMemcpyAsync(base + L.riters, iters, sizeof(int) * N, hipMemcpyDeviceToDevice, s)) !=
-        hipSuccess)
-      return e;
   return launch_update<T>(n, N, Xf, Xa, Wd, 1, s);
 }
 
@@ -1221,23 +1593,13 @@ hipError_t launch_senkf(int n, int m, int N, int k, const T* Xf, T* Xa, const in
   if (L.rNP == 128)
     return launch_senkf_mfma<T, 128>(n, m, N, k, Xf, Xa, idx, hw, y, rdiag, eps, ws, L, iters0,
                                      s);
-  // N > 128: the row-block partials with FP64 sums
-  unsigned char* base = (unsigned char*)ws;
-  double* part = (double*)(base + L.rpart);
-  double* G = (double*)(base + L.rG);
-  double* B = (double*)(base + L.rB);
-  int* err = (int*)(base + L.err);
-  const size_t sh = sizeof(double) * (2 * (size_t)L.RB * N + 2 * L.RB);
-  hipError_t e = launch_zero_u32((unsigned*)err, 1, s);
+  const hipError_t e = red_wide_product<T, true>(n, m, N, k, Xf, idx, hw, y, rdiag, eps, ws, L, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_red_gram<T, true>), dim3(L.nwg_max), dim3(kBlock), sh, s, n, m, N, k,
-                     L.RB, L.nblk, Xf, idx, hw, y, rdiag, eps, part, err);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_red_sum, dim3((N * N + kBlock - 1) / kBlock), dim3(kBlock), 0, s, N,
-                     L.nwg_max, part, G, B, N * N, 0.0);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (iters0 && (e = launch_zero_u32((unsigned*)iters0, N, s)) != hipSuccess) return e;
-  return launch_update<T>(n, N, Xf, Xa, B, 0, s, nullptr);
+  if (iters0) {
+    const hipError_t ez = launch_zero_u32((unsigned*)iters0, N, s);
+    if (ez != hipSuccess) return ez;
+  }
+  return launch_update<T>(n, N, Xf, Xa, (const double*)((unsigned char*)ws + L.rB), 0, s, nullptr);
 }
 
 template <typename T>
