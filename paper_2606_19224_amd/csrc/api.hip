@@ -169,6 +169,27 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       if ((size_t)L.splitP * L.splitMs > rows) rows = (size_t)L.splitP * L.splitMs;
       L.gerr = L.xwords ? take(sizeof(int) * (rows / 8 + 1)) : 0;
     }
+    // FP64 column solver past N = 64: no other solver's partials are live with
+    // it, so its buffers lie on partG .. partW when those are large enough
+    // (all but small m, and m past 16 N^2), else behind everything
+    if (prec == CGD_FP64 && N > 64 && N <= 128 && (L.wrows = columns_wide_rows(m)) > 0) {
+      const size_t rows = (size_t)L.wrows, sizes[7] = {
+          sizeof(double) * rows * 128, sizeof(double) * N * rows, sizeof(double) * N * rows,
+          sizeof(double) * N * rows,   sizeof(double) * N * rows, sizeof(double) * rows,
+          sizeof(int) * (rows / 8 + 1)};
+      size_t* offs[7] = {&L.wS, &L.wD, &L.wZ, &L.wR, &L.wP, &L.wRp, &L.wgerr};
+      size_t need = 0;
+      for (size_t b : sizes) need += al256(b);
+      size_t at = L.partG;
+      if (need > L.col - L.partG) {
+        at = o;
+        o += need;
+      }
+      for (int q = 0; q < 7; ++q) {
+        *offs[q] = at;
+        at += al256(sizes[q]);
+      }
+    }
     // row-block x member-group solver (FP32 only)
     if (prec_tile(prec) && tile_shape(m, N, &L.tNP, &L.tRB, &L.tNG, &L.tnblk)) {
       L.tx = take(sizeof(unsigned long long) * tile_words(L.tNP, L.tNG, L.tnblk));
@@ -272,6 +293,8 @@ cgd_status common_checks(int n, int m, int N, int k, const void* Xf, void* Xa, c
 //           slice fits and the N * P workgroups fit co-resident;
 //   kind 3: column-parallel solver (one workgroup per member, S through L2)
 //           when the column layout applies and N workgroups fit co-resident;
+//           in FP64 for 64 < N <= 128 as well, without waits (any grid runs),
+//           never on request (solver = 3 keeps its range);
 //   kind 5: row-block x member-group solver (FP32, N <= 128, cold start,
 //           no stall fallback) when its NG * nblk workgroups fit co-resident;
 //   kind 2: resident row-block solver when N and the row blocks fit on chip
@@ -331,6 +354,13 @@ cgd_status choose_solver(int m, int N, const Opts& o, const Layout& L,
       return CGD_OK;
     }
     if (o.solver == 3) return CGD_ERR_UNSUPPORTED;
+  }
+  if (o.solver == 0 && L.wrows > 0) {
+    c.kind = 3;
+    c.NP = 128;
+    c.nwg = N;
+    *out = c;
+    return CGD_OK;
   }
   if (mix) {
     // the mixed mode runs on the row-block x member-group solver (BF16 inner
@@ -448,6 +478,19 @@ cgd_status run_full(int n, int m, int N, int k, const void* Xf, void* Xa, const 
   const cgd_status cs = choose_solver<T>(m, N, o, L, &sc);
   if (cs != CGD_OK) return cs;
   hipEvent_t* ev = (hipEvent_t*)o.prof_events;
+  if constexpr (sizeof(T) == 8) {
+    if (sc.kind == 3 && L.wrows > 0) {
+      a.D = (T*)(b + L.wD);
+      a.gerr = (int*)(b + L.wgerr);  // the gather also clears the error word
+      if (launch_cg_columns_wide(a, (T*)(b + L.wS), (T*)(b + L.wZ), (T*)(b + L.wR),
+                                 (T*)(b + L.wP), (T*)(b + L.wRp), ev, s) != hipSuccess)
+        return CGD_ERR_HIP;
+      if (ev && hipEventRecord(ev[1], s) != hipSuccess) return CGD_ERR_HIP;
+      if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, nullptr) != hipSuccess)
+        return CGD_ERR_HIP;
+      return unscale_z_out<T>(m, N, r, o, s);
+    }
+  }
   if (sc.kind == 3 || sc.kind == 4) {
     // two launches: the gather (which also clears the published-W words, the
     // exchange slots and the error word) and the solver, which also applies
@@ -1275,6 +1318,16 @@ int cgd_layout_selfcheck(int n, int m, int N, int k, int prec) {
     need(L.xw, sizeof(unsigned long long) * (2 * NN + split_exchange_words(N, L.splitP) + 1));
     need(L.Ssplit, esz * rows * np);
     need(L.Dsplit, esz * (size_t)N * rows);
+  }
+  // FP64 column solver past N = 64: its buffers, one after another, end inside
+  // the partials or the workspace and leave the results alone
+  if (L.wrows > 0) {
+    const size_t rows = (size_t)L.wrows, end = L.wgerr + sizeof(int) * (rows / 8 + 1);
+    if (L.wS < L.partG || end > L.total || (L.wS < L.col && end > L.col)) ++bad;
+    if (L.wrows < m || L.wD - L.wS < 8 * rows * 128 || L.wZ - L.wD < 8 * N * rows ||
+        L.wR - L.wZ < 8 * N * rows || L.wP - L.wR < 8 * N * rows ||
+        L.wRp - L.wP < 8 * N * rows || L.wgerr - L.wRp < 8 * rows)
+      ++bad;
   }
   // row-block x member-group solver: its exchange words (cleared whole every
   // launch), NG * nblk workgroups covering the rows and the members

@@ -1272,6 +1272,20 @@ hipError_t launch_mix(const CGArgs<T>& a, const ColArgs<T>& vec, hipEvent_t* ev,
   return hipErrorInvalidValue;
 }
 
+// FP64 for 64 < N <= 128: the same recurrence, one workgroup per member, with
+// the update as a launch of its own, so that no workgroup waits for another
+// (any grid runs, whatever else holds the GPU).  Bound: each member's pass
+// over S (m x 128 doubles) through its CU's path to L2, 64 bytes a clock:
+// at m = 4093, N = 100 the streaming solver's grid-wide barriers and row
+// blocks took 275 us a step.
+template <typename T, int NP, bool GV>
+__global__ __launch_bounds__(kCB) void k_cg_columns_wide(CGArgs<T> a, ColArgs<T> ca) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  CGD_TRACE(0);
+  fold_gather_errors(a);
+  column_phase<T, NP, false, GV, false, false>(a, ca, blockIdx.x, smem_raw);
+}
+
 // ---------------------------------------------------------------------------
 // Batched mode: many independent problems, each solved as above (the same
 // per-member recurrence, stop rule and update), in three launches over work
@@ -1456,6 +1470,44 @@ hipError_t launch_split_np(const CGArgs<T>& a, int P, int ms, T* Sg, T* Dg,
 }
 
 }  // namespace
+
+namespace {
+template <bool GV>
+hipError_t launch_wide(const CGArgs<double>& a, ColArgs<double> ca, hipEvent_t* ev,
+                       hipStream_t s) {
+  using K = KC<double, 128, false>;
+  col_shape<double, 128, false, GV>(a.m, &ca.mp, &ca.RL);
+  CGArgs<double> a2 = a;
+  hipError_t e = launch_gather<double, 128, false, false>(a, ca, &a2.ngerr, s);
+  if (e != hipSuccess) return e;
+  if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;  // the solver launch alone
+  const size_t sh = (GV ? 0 : sizeof(double) * 5 * (size_t)ca.mp) + K::fixed +
+                    sizeof(double) * (size_t)ca.RL * 128;
+  auto fn = k_cg_columns_wide<double, 128, GV>;
+  e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(fn, dim3(a.N), dim3(kCB), sh, s, a2, ca);
+  return hipGetLastError();
+}
+}  // namespace
+
+int columns_wide_rows(int m) {
+  using K = KC<double, 128, false>;
+  return m > kColumnsMaxRows ? 0 : (m + K::RG - 1) / K::RG * K::RG;
+}
+
+hipError_t launch_cg_columns_wide(const CGArgs<double>& a, double* Sp, double* Vz, double* Vr,
+                                  double* Vp, double* Rp, hipEvent_t* ev, hipStream_t s) {
+  ColArgs<double> ca = {};
+  ca.Sp = Sp;
+  ca.Dt = a.D;
+  if (col_lds_vectors<double, 128, false>(a.m)) return launch_wide<false>(a, ca, ev, s);
+  ca.Vz = Vz;
+  ca.Vr = Vr;
+  ca.Vp = Vp;
+  ca.Rp = Rp;
+  return launch_wide<true>(a, ca, ev, s);
+}
 
 // Column solver geometry for the workspace: padded rows and padded N, or 0
 // when the column solver does not apply to (m, N, prec).  mix selects the

@@ -149,6 +149,10 @@ struct Layout {
   int mp, NPc;     // column solver: padded rows and padded N (0 if not applicable)
   size_t Vz, Vr, Vp, Rp;  // column solver with vectors in global memory (0 otherwise)
   int gv;
+  // FP64 column solver for 64 < N <= 128: padded rows (0 if not applicable)
+  // and its buffers, which share the row-block solvers' partials where they fit
+  int wrows;
+  size_t wS, wD, wZ, wR, wP, wRp, wgerr;
   size_t xflags, pend, err;
   int NP;  // partial/Gram stride: max(N, resident padding of N)
   // reduced mode (rNP != 0: N <= 128, with Q = [P | Yt] at rQ and (W - I)^T at
@@ -192,6 +196,13 @@ int columns_coresident(int m, int N, int mix);
 template <typename T>
 hipError_t launch_cg_columns(const CGArgs<T>& a, T* Sp, __bf16* Sh, unsigned long long* wb,
                              T* Vz, T* Vr, T* Vp, T* Rp, hipEvent_t* ev, hipStream_t s);
+// The column solver in FP64 for 64 < N <= 128 (update by launch_update, no
+// workgroup waits for another): S padded to rows x 128, D^T, z, r, p (N x
+// rows each) and diag(R) (rows).  columns_wide_rows: padded rows, 0 when m is
+// out of range.
+int columns_wide_rows(int m);
+hipError_t launch_cg_columns_wide(const CGArgs<double>& a, double* Sp, double* Vz, double* Vr,
+                                  double* Vp, double* Rp, hipEvent_t* ev, hipStream_t s);
 // Split solver (cg_columns.hip): a gather launch writing S in slices (Sg,
 // P * ms * NP) and D transposed (Dg, N x P * ms), then P workgroups per
 // member, each with its ms rows of S in LDS, partial sums exchanged once per
