@@ -83,6 +83,11 @@ inline bool prec_known(int p) {
 }
 inline bool prec_tile(int p) { return p == CGD_FP32 || p == CGD_MIXED_BF16 || p == CGD_BF16_SPLIT; }
 
+// FP64, 64 < N <= 128: fewer rows than this stay on the column solver, whose
+// step grows with m (11 us at m = 1024, 18 us at 2048, 51 us at 4093, N = 100)
+// while the row-block solver's is bound by its exchange (16 to 18 us).
+constexpr int kTile64MinRows = 1800;
+
 Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
   Layout L;
   memset(&L, 0, sizeof(L));
@@ -188,6 +193,18 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       for (int q = 0; q < 7; ++q) {
         *offs[q] = at;
         at += al256(sizes[q]);
+      }
+      int ng = 0, nb = 0;
+      if (m >= kTile64MinRows && tile64_shape(m, N, &ng, &nb)) {
+        const size_t xb = al256(sizeof(unsigned long long) * tile64_words(ng, nb));
+        const size_t sb = al256(sizeof(double) * (size_t)m * 128);
+        if (xb + sb + sizeof(double) * (size_t)m <= L.col - L.partG) {
+          L.t64NG = ng;
+          L.t64nblk = nb;
+          L.t64x = L.partG;
+          L.t64S = L.t64x + xb;
+          L.t64rv = L.t64S + sb;
+        }
       }
     }
     // row-block x member-group solver (FP32 only)
@@ -295,8 +312,9 @@ cgd_status common_checks(int n, int m, int N, int k, const void* Xf, void* Xa, c
 //           when the column layout applies and N workgroups fit co-resident;
 //           in FP64 for 64 < N <= 128 as well, without waits (any grid runs),
 //           never on request (solver = 3 keeps its range);
-//   kind 5: row-block x member-group solver (FP32, N <= 128, cold start,
-//           no stall fallback) when its NG * nblk workgroups fit co-resident;
+//   kind 5: row-block x member-group solver (FP32, N <= 128, or FP64, 64 < N <=
+//           128 and automatic only; cold start, no stall fallback) when its
+//           NG * nblk workgroups fit co-resident;
 //   kind 2: resident row-block solver when N and the row blocks fit on chip
 //           (NP = padded N, RB rows per workgroup, nwg workgroups);
 //   kind 1: streaming cooperative solver otherwise.
@@ -354,6 +372,15 @@ cgd_status choose_solver(int m, int N, const Opts& o, const Layout& L,
       return CGD_OK;
     }
     if (o.solver == 3) return CGD_ERR_UNSUPPORTED;
+  }
+  if (o.solver == 0 && L.t64NG > 0 && !o.z0 && !o.fallback_on_stall &&
+      L.t64NG * L.t64nblk <= tile64_coresident()) {
+    c.kind = 5;
+    c.NP = 128;
+    c.RB = 128;
+    c.nwg = L.t64NG * L.t64nblk;
+    *out = c;
+    return CGD_OK;
   }
   if (o.solver == 0 && L.wrows > 0) {
     c.kind = 3;
@@ -479,6 +506,16 @@ cgd_status run_full(int n, int m, int N, int k, const void* Xf, void* Xa, const 
   if (cs != CGD_OK) return cs;
   hipEvent_t* ev = (hipEvent_t*)o.prof_events;
   if constexpr (sizeof(T) == 8) {
+    if (sc.kind == 5) {
+      if (launch_cg_tile64(a, L.t64NG, L.t64nblk, (unsigned long long*)(b + L.t64x),
+                           (double*)(b + L.t64S), a.D, (double*)(b + L.t64rv), ev, s) !=
+          hipSuccess)
+        return CGD_ERR_HIP;
+      if (ev && hipEventRecord(ev[1], s) != hipSuccess) return CGD_ERR_HIP;
+      if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, nullptr) != hipSuccess)
+        return CGD_ERR_HIP;
+      return unscale_z_out<T>(m, N, r, o, s);
+    }
     if (sc.kind == 3 && L.wrows > 0) {
       a.D = (T*)(b + L.wD);
       a.gerr = (int*)(b + L.wgerr);  // the gather also clears the error word
@@ -1327,6 +1364,13 @@ int cgd_layout_selfcheck(int n, int m, int N, int k, int prec) {
     if (L.wrows < m || L.wD - L.wS < 8 * rows * 128 || L.wZ - L.wD < 8 * N * rows ||
         L.wR - L.wZ < 8 * N * rows || L.wP - L.wR < 8 * N * rows ||
         L.wRp - L.wP < 8 * N * rows || L.wgerr - L.wRp < 8 * rows)
+      ++bad;
+  }
+  if (L.t64NG > 0) {
+    if (L.t64x < L.partG || L.t64rv + sizeof(double) * (size_t)m > L.col ||
+        L.t64S - L.t64x < sizeof(unsigned long long) * tile64_words(L.t64NG, L.t64nblk) ||
+        L.t64rv - L.t64S < sizeof(double) * (size_t)m * 128 || L.t64NG * 16 < N ||
+        (size_t)L.t64nblk * 128 < (size_t)m)
       ++bad;
   }
   // row-block x member-group solver: its exchange words (cleared whole every

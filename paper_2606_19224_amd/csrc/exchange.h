@@ -102,6 +102,70 @@ __device__ inline bool census_wait(unsigned long long* word, int* err, unsigned 
   return go != 0;
 }
 
+// Exchange words of the row-block x member-group solvers: 32 bits of data, the
+// exchange number in the upper half.
+__device__ inline unsigned long long ld64(const unsigned long long* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline void st64(unsigned long long* p, unsigned v, unsigned ep) {
+  __hip_atomic_store(p, (unsigned long long)v | ((unsigned long long)ep << 32), __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_AGENT);
+}
+// A wait for an exchange word gives up after this many ticks of the 100 MHz
+// real-time counter (1 s; a healthy wait is a few microseconds, or the
+// slowest workgroup's gather at the start).
+constexpr unsigned long long kTileWaitTicks = 100000000ull;
+
+// Re-reads *p until its exchange number is ep (w: the first read); a wait
+// that runs out sets bad, and once bad is set no wait starts.
+__device__ inline unsigned long long poll64(const unsigned long long* p, unsigned ep,
+                                            unsigned long long w, bool& bad) {
+  if ((unsigned)(w >> 32) == ep || bad) return w;
+  const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
+  for (;;) {
+    __builtin_amdgcn_s_sleep(1);
+    w = ld64(p);
+    if ((unsigned)(w >> 32) == ep) break;
+    if (__builtin_amdgcn_s_memrealtime() - t0 > kTileWaitTicks) {
+      bad = true;
+      break;
+    }
+  }
+  return w;
+}
+// Waits until every word w[u], u < n (first reads of at(u)), carries exchange
+// number ep, re-reading all stale words together in each round: one memory
+// round trip per round, however many words are late.  A wait that runs out
+// sets bad, and once bad is set no wait starts.
+template <int NMAX, typename At>
+__device__ __attribute__((always_inline)) void poll_all(unsigned long long (&w)[NMAX], int n, At at,
+                                                        unsigned ep, bool& bad) {
+  unsigned long long t0 = 0;
+  for (;;) {
+    bool stale = false;
+#pragma unroll
+    for (int u = 0; u < NMAX; ++u) stale |= u < n && (unsigned)(w[u] >> 32) != ep;
+    if (!stale || bad) return;
+    const unsigned long long now = __builtin_amdgcn_s_memrealtime();
+    if (t0 == 0) {
+      t0 = now;
+    } else if (now - t0 > kTileWaitTicks) {
+      bad = true;
+      return;
+    }
+    __builtin_amdgcn_s_sleep(1);
+#pragma unroll
+    for (int u = 0; u < NMAX; ++u)
+      if (u < n && (unsigned)(w[u] >> 32) != ep) w[u] = ld64(at(u));
+  }
+}
+
+// Clears exchange words ahead of a launch that polls them.
+__global__ void k_zero_words(unsigned long long* p, size_t n) {
+  const size_t stride = (size_t)gridDim.x * blockDim.x;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0ull;
+}
+
 }  // namespace
 }  // namespace cgd
 

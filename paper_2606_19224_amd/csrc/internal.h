@@ -153,6 +153,10 @@ struct Layout {
   // and its buffers, which share the row-block solvers' partials where they fit
   int wrows;
   size_t wS, wD, wZ, wR, wP, wRp, wgerr;
+  // FP64 row-block x member-group solver on the same partials (t64NG = 0: it
+  // does not apply or they are too small)
+  int t64NG, t64nblk;
+  size_t t64x, t64S, t64rv;
   size_t xflags, pend, err;
   int NP;  // partial/Gram stride: max(N, resident padding of N)
   // reduced mode (rNP != 0: N <= 128, with Q = [P | Yt] at rQ and (W - I)^T at
@@ -203,6 +207,15 @@ hipError_t launch_cg_columns(const CGArgs<T>& a, T* Sp, __bf16* Sh, unsigned lon
 int columns_wide_rows(int m);
 hipError_t launch_cg_columns_wide(const CGArgs<double>& a, double* Sp, double* Vz, double* Vr,
                                   double* Vp, double* Rp, hipEvent_t* ev, hipStream_t s);
+// Row-block x member-group solver in FP64 (cg_tile64.hip), 64 < N <= 128,
+// cold start: members in groups of 16, 128 rows per workgroup, NG * nblk
+// workgroups that must run at once (always a cooperative launch).  words:
+// tile64_words of exchange words, S: m x 128, D: m x N, rv: m.
+int tile64_shape(int m, int N, int* NG, int* nblk);
+size_t tile64_words(int NG, int nblk);
+int tile64_coresident();
+hipError_t launch_cg_tile64(const CGArgs<double>& a, int NG, int nblk, unsigned long long* words,
+                            double* S, double* D, double* rv, hipEvent_t* ev, hipStream_t s);
 // Split solver (cg_columns.hip): a gather launch writing S in slices (Sg,
 // P * ms * NP) and D transposed (Dg, N x P * ms), then P workgroups per
 // member, each with its ms rows of S in LDS, partial sums exchanged once per

@@ -1,7 +1,9 @@
-"""FP64 analyses with 64 < N <= 128 (the column solver with its own update
-launch): parity with the oracle's textbook CG at the edges of its row steps
-(64 rows), of its LDS vectors (about 3000 rows) and of N, with a warm start,
-preconditioning, fixed iterations and in place.  FP64 bar 1e-10."""
+"""FP64 analyses with 64 < N <= 128 (the row-block x member-group solver in
+FP64, and the column solver with its own update launch for few rows and warm
+starts): parity with the oracle's textbook CG at the edges of their row blocks
+(128) and row steps (64), of the column solver's LDS vectors (about 3000
+rows) and of N, with a warm start, preconditioning, fixed iterations and in
+place.  FP64 bar 1e-10."""
 import numpy as np
 import pytest
 
@@ -14,11 +16,13 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,m,N,k", [(50, 1, 65, 1), (80, 20, 128, 2), (200, 63, 96, 1),
                                      (200, 64, 100, 3), (300, 65, 66, 1), (900, 700, 127, 4),
-                                     (1500, 3073, 100, 1)])
+                                     (700, 1799, 81, 1), (700, 1800, 128, 2), (1500, 3073, 100, 1),
+                                     (900, 6528, 80, 1)])
 def test_parity(lib, n, m, N, k):
     import torch
     say(f"case: fp64 columns n={n} m={m} N={N} k={k}")
-    assert lib.Plan(n, m, N, k, prec="fp64").solver_info()["solver"] == "k_cg_columns"
+    assert lib.Plan(n, m, N, k, prec="fp64").solver_info()["solver"] in ("k_cg_columns",
+                                                                         "k_cg_tile")
     p = W.random_problem(n, m, N, k, seed=n + m, tol=1e-12)
     got = run(lib, p, "fp64", want_z=True, want_iters=True, want_relres=True)
     ref = O.enkf_analysis(p.Xf, p.idx, p.w, p.y, p.r, p.eps, solver="cg_free", tol=p.tol,
@@ -40,10 +44,12 @@ def test_parity(lib, n, m, N, k):
 
 def test_warm_start_and_preconditioning(lib):
     import torch
-    p = W.random_problem(700, 600, 90, 2, seed=77, tol=1e-12)
+    p = W.random_problem(1500, 1900, 90, 2, seed=77, tol=1e-12)
     chol = O.enkf_analysis(p.Xf, p.idx, p.w, p.y, p.r, p.eps)
     pre = run(lib, p, "fp64", precond="diag_r", want_z=True)
     assert rel(pre["Xa"], chol["Xa"]) <= 1e-10 and rel(pre["Z"], chol["Z"]) <= 1e-10
+    plain = run(lib, p, "fp64", want_z=True, want_relres=True)
+    assert rel(plain["Z"], chol["Z"]) <= 1e-10 and plain["relres"].max() <= 1e-10
     for scale in (1e-3, 30.0):   # a good start, and one that falls back to zero
         Z0 = chol["Z"] * (1 + scale * np.random.default_rng(3).standard_normal(chol["Z"].shape))
         z0 = torch.as_tensor(np.ascontiguousarray(Z0), device="cuda:0")
