@@ -168,34 +168,49 @@ __global__ __launch_bounds__(kBlock) void k_update_mfma(int n, int N, const T* X
 // The same update with the A' operand read from global memory straight into
 // the MFMA's registers: no tile of X_f passes through LDS and no barrier is
 // taken per tile.  W'^T sits in LDS (from Wd as update_load_w forms it, or, WT,
-// already transposed in T as k_red_update takes it).  Each wave takes 16-row
-// blocks in turn over the whole grid (workgroups first, then their waves); lane (lr, lk) holds row lr's columns
-// lk NP/4 .. lk NP/4 + NP/4 - 1 (16-byte loads: N a multiple of 16/sizeof(T),
-// X_f and X_a 16-byte aligned), the permutation of the summation index the B
-// operand uses too.  Mode 0 centres each row with its mean (the lane's part
-// plus two shuffles across the row's four lanes).  X_f is read again for the
-// output elements before the block's stores, so X_a may alias X_f.
+// already transposed in T as k_red_update takes it, of row stride WS).  Each
+// wave takes 16-row blocks in turn over the whole grid (workgroups first, then
+// their waves); lane (lr, lk) holds row lr's columns 4 VU s + VU lk + u, the
+// permutation of the summation index the B operand uses too, so that a load
+// instruction reads 64 consecutive bytes of each row (16-byte loads: N a
+// multiple of VU = 16/sizeof(T), X_f and X_a 16-byte aligned).  (Runs of NP/4
+// columns per lane fetched each 128-byte line eight times, past the L1: 98 us
+// against 71 us at n = 10^5, N = 100 in FP64, padded to 112 as well; 36 against 33 us
+// at n = 65536, N = 128 in FP32.)  NP is N rounded up to 16 here.  Mode 0
+// centres each row with its mean (the lane's part plus two shuffles across the
+// row's four lanes).  X_f is read again for the output elements before the
+// block's stores, so X_a may alias X_f.
 constexpr int kUpdWaves = 8;
 
 template <typename T, int NP, bool WT>
-__global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, const T* Xf, T* Xa,
-                                                               const double* Wd, const T* Wtg,
-                                                               int mode, const int* skip) {
+__global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, int WS, const T* Xf,
+                                                               T* Xa, const double* Wd,
+                                                               const T* Wtg, int mode,
+                                                               const int* skip) {
   using U = UCfg<T, NP>;
   using V = typename Vec4<T>::type;
   constexpr int KQ = NP / 4, TJ = NP / 16, VU = 16 / (int)sizeof(T), BS = 64 * kUpdWaves;
-  constexpr int CH = KQ < 8 ? KQ : 8;  // B operand loads in chunks (register pressure)
+  constexpr int UN = TJ % 2 == 0 ? 2 : 1;  // (an odd count would unroll whole, and spill)
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (skip && (*skip & 4)) return;
   T* Wt = (T*)smem_raw;  // NP x LD
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lk = lane >> 4;
   if constexpr (WT) {
-    for (int e = tid; e < NP * NP / VU; e += BS) {
-      const int row = e / (NP / VU), c = (e - row * (NP / VU)) * VU;
-      T v[VU];
-      vload<VU>(Wtg + (size_t)row * NP + c, v);
+    constexpr int NC = NP * NP / VU, UL = 8;  // 16-byte chunks, loads in flight per thread
+    for (int e0 = tid; e0 < NC; e0 += BS * UL) {
+      T v[UL][VU];
 #pragma unroll
-      for (int u = 0; u < VU; ++u) Wt[row * U::LD + c + u] = v[u];
+      for (int u = 0; u < UL; ++u) {
+        const int e = e0 + u * BS, row = e / (NP / VU), c = (e - row * (NP / VU)) * VU;
+        if (e < NC) vload<VU>(Wtg + (size_t)row * WS + c, v[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < UL; ++u) {
+        const int e = e0 + u * BS, row = e / (NP / VU), c = (e - row * (NP / VU)) * VU;
+        if (e < NC)
+#pragma unroll
+          for (int q = 0; q < VU; ++q) Wt[row * U::LD + c + q] = v[u][q];
+      }
     }
   } else {
     update_load_w<T, NP, BS>(N, Wd, mode, Wt);
@@ -206,11 +221,11 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, co
   const int nb = (n + 15) / 16, step = gridDim.x * kUpdWaves;
   for (int b = blockIdx.x + gridDim.x * wv; b < nb; b += step) {
     const int i0 = b * 16, row = i0 + lr;
-    // A' operand: this lane's quarter of row lr, zero past N and past n
+    // A' operand: this lane's columns of row lr, zero past N and past n
     T av[KQ];
 #pragma unroll
     for (int c = 0; c < KQ; c += VU) {
-      const int col = lk * KQ + c;
+      const int col = 4 * c + VU * lk;
       if (row < n && col < N) {
         vload<VU>(Xf + (size_t)row * N + col, *reinterpret_cast<T(*)[VU]>(&av[c]));
       } else {
@@ -227,11 +242,11 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, co
       const double mu = sum / N;
 #pragma unroll
       for (int t = 0; t < KQ; ++t)
-        av[t] = lk * KQ + t < N ? (T)((double)av[t] - mu) : (T)0;
+        av[t] = 4 * (t - t % VU) + VU * lk < N ? (T)((double)av[t] - mu) : (T)0;
     }
     // every X_f element of the block's rows is in registers (av) or read below
     // before this wave stores any of them
-#pragma unroll 2
+#pragma unroll UN
     for (int tj = 0; tj < TJ; ++tj) {
       // X_f at this lane's output elements of the tile (rows frag_row(lk, i),
       // column lr), requested before the tile's products
@@ -241,15 +256,19 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, co
         const int r = i0 + frag_row<T>(lk, i), col = tj * 16 + lr;
         xo[i] = (r < n && col < N) ? Xf[(size_t)r * N + col] : (T)0;
       }
-      V acc = {0, 0, 0, 0};
-      const T* wrow = Wt + (tj * 16 + lr) * U::LD + lk * KQ;
+      V acc = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};  // two chains
+      const T* wrow = Wt + (tj * 16 + lr) * U::LD + VU * lk;
 #pragma unroll
-      for (int t0 = 0; t0 < KQ; t0 += CH) {
-        T bv[CH];
-        vload<CH>(wrow + t0, bv);
+      for (int t0 = 0; t0 < KQ; t0 += VU) {
+        T bv[VU];
+        vload<VU>(wrow + 4 * t0, bv);
 #pragma unroll
-        for (int t = 0; t < CH; ++t) acc = mfma4(av[t0 + t], bv[t], acc);
+        for (int t = 0; t < VU; t += 2) {
+          acc = mfma4(av[t0 + t], bv[t], acc);
+          acc1 = mfma4(av[t0 + t + 1], bv[t + 1], acc1);
+        }
       }
+      acc += acc1;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = i0 + frag_row<T>(lk, i), col = tj * 16 + lr;
@@ -272,8 +291,8 @@ bool update_rows_ok(int n, int N, const T* Xf, const T* Xa) {
 }
 
 template <typename T, int NP, bool WT>
-hipError_t launch_update_rows(int n, int N, const T* Xf, T* Xa, const double* Wd, const T* Wt,
-                              int mode, const int* skip, hipStream_t s) {
+hipError_t launch_update_rows_np(int n, int N, int WS, const T* Xf, T* Xa, const double* Wd,
+                                 const T* Wt, int mode, const int* skip, hipStream_t s) {
   using U = UCfg<T, NP>;
   constexpr size_t lds = sizeof(T) * (size_t)NP * U::LD;
   const void* fn = (const void*)k_update_rows<T, NP, WT>;
@@ -295,8 +314,25 @@ hipError_t launch_update_rows(int n, int N, const T* Xf, T* Xa, const double* Wd
   const int nb = (n + 15) / 16;
   const int grid = nb < resident ? nb : resident;
   hipLaunchKernelGGL((k_update_rows<T, NP, WT>), dim3(grid), dim3(64 * kUpdWaves), lds, s, n, N,
-                     Xf, Xa, Wd, Wt, mode, skip);
+                     WS, Xf, Xa, Wd, Wt, mode, skip);
   return hipGetLastError();
+}
+
+// N <= 128 padded to 16, 32, 48, 64, 96, 112 or 128 (the products' cost goes
+// with the square of it); WS: row stride of Wt (WT only).
+template <typename T, bool WT>
+hipError_t launch_update_rows(int n, int N, int WS, const T* Xf, T* Xa, const double* Wd,
+                              const T* Wt, int mode, const int* skip, hipStream_t s) {
+#define CGD_UPD_NP(NP) \
+  if (N <= NP) return launch_update_rows_np<T, NP, WT>(n, N, WS, Xf, Xa, Wd, Wt, mode, skip, s)
+  CGD_UPD_NP(16);
+  CGD_UPD_NP(32);
+  CGD_UPD_NP(48);
+  CGD_UPD_NP(64);
+  CGD_UPD_NP(96);
+  CGD_UPD_NP(112);
+#undef CGD_UPD_NP
+  return launch_update_rows_np<T, 128, WT>(n, N, WS, Xf, Xa, Wd, Wt, mode, skip, s);
 }
 
 template <typename T, int NP>
@@ -1308,14 +1344,8 @@ inline int update_rows(int N) {
 template <typename T>
 hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int mode,
                          hipStream_t s, const int* skip) {
-  if (update_rows_ok(n, N, Xf, Xa)) {
-    if (N <= 16) return launch_update_rows<T, 16, false>(n, N, Xf, Xa, Wd, nullptr, mode, skip, s);
-    if (N <= 32) return launch_update_rows<T, 32, false>(n, N, Xf, Xa, Wd, nullptr, mode, skip, s);
-    if (N <= 64) return launch_update_rows<T, 64, false>(n, N, Xf, Xa, Wd, nullptr, mode, skip, s);
-    if constexpr (sizeof(T) == 4)
-      if (N <= 128)
-        return launch_update_rows<T, 128, false>(n, N, Xf, Xa, Wd, nullptr, mode, skip, s);
-  }
+  if (N <= 128 && update_rows_ok(n, N, Xf, Xa))
+    return launch_update_rows<T, false>(n, N, 0, Xf, Xa, Wd, nullptr, mode, skip, s);
   if (N <= 16) return launch_update_mfma<T, 16>(n, N, Xf, Xa, Wd, mode, skip, s);
   if (N <= 32) return launch_update_mfma<T, 32>(n, N, Xf, Xa, Wd, mode, skip, s);
   if (N <= 64) return launch_update_mfma<T, 64>(n, N, Xf, Xa, Wd, mode, skip, s);
@@ -1409,7 +1439,7 @@ hipError_t launch_red_update(int n, int N, const T* Xf, T* Xa, const T* Wt, hipS
 template <typename T, int NP>
 hipError_t launch_red_update_np(int n, int N, const T* Xf, T* Xa, const T* Wt, hipStream_t s) {
   if (update_rows_ok(n, N, Xf, (const T*)Xa))
-    return launch_update_rows<T, NP, true>(n, N, Xf, Xa, nullptr, Wt, 1, nullptr, s);
+    return launch_update_rows<T, true>(n, N, NP, Xf, Xa, nullptr, Wt, 1, nullptr, s);
   constexpr size_t lmax = 160 * 1024;
   if constexpr (UCfg<T, NP, 64>::lds <= lmax)
     if (n >= 64 * 256) return launch_red_update<T, NP, 64>(n, N, Xf, Xa, Wt, s);
