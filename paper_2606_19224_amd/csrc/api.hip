@@ -221,8 +221,7 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       L.rKC = kc;
       L.rS = sc;
       const size_t lg = np < 64 ? 64 : (size_t)np, nr = lg;
-      L.rQ = np > 64 ? take(esz * (size_t)mpad * 2 * np) : 0;  // NP <= 64: Q stays on chip
-      L.rpart = take(esz * (size_t)sc * np * 2 * np);
+      L.rpart = take(esz * (size_t)sc * reduced_part_elems(m, N));  // Q stays on chip
       L.rG = take(sizeof(double) * nr * lg);
       L.rWt = take(esz * (size_t)np * np);
       L.rerr = take(sizeof(int) * (size_t)mpad);  // one word per gather workgroup

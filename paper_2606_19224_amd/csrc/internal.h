@@ -159,8 +159,8 @@ struct Layout {
   size_t t64x, t64S, t64rv;
   size_t xflags, pend, err;
   int NP;  // partial/Gram stride: max(N, resident padding of N)
-  // reduced mode (rNP != 0: N <= 128, with Q = [P | Yt] at rQ and (W - I)^T at
-  // rWt; otherwise N > 128 padded to rWNP, G of stride rLG)
+  // reduced mode (rNP != 0: N <= 128, (W - I)^T at rWt; otherwise N > 128 padded
+  // to rWNP, Q = [P | Yt] at rQ, G of stride rLG)
   size_t rpart, rG, rB, riters, rstat, rQ, rWt, rerr;
   // non-diagonal R (mode bit 2): whitening scratch and substitute inputs
   size_t tSd, tDd, tXp, tEp, tidx, tw, ty, tr, tzt, terr;
@@ -271,10 +271,11 @@ hipError_t launch_unscale_rows(int m, int N, T* z, const T* rdiag, hipStream_t s
 template <typename T>
 hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int mode,
                          hipStream_t s, const int* skip = nullptr);
-// Geometry of the reduced mode's MFMA path (N <= 128): N padded to NP (32,
-// 64 or 128), m padded to mpad (a multiple of 32), KC rows per chunk of the
-// N x 2N product and S chunks.  0 when N is out of range.
+// Geometry of the reduced mode for N <= 128: N padded to NP (32, 64 or 128), m
+// padded to mpad (a multiple of 32), KC rows per chunk of the N x 2N product
+// and S parts of it.  0 when N is out of range.
 int reduced_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
+size_t reduced_part_elems(int m, int N);  // elements of one chunk's (or workgroup's) part
 // The same for N > 128: NP a multiple of 64, mpad, KC and S as above.
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
 // Xg (ng rows) is the array the observations are gathered from; Xf is

@@ -1,4 +1,6 @@
 // Ensemble update, CGD-EnKF-Reduced and input validation kernels (gfx950).
+#include <type_traits>
+
 #include "modes.h"
 #include "mfma_util.h"
 #include "update_tile.h"
@@ -454,117 +456,29 @@ __global__ __launch_bounds__(kBlock) void k_small_cg(int N, const double* G, con
 //   l_i  = sqrt((N-1) r_i),  zbar_i = HX_i 1 / N,
 // zero in the padding columns and rows.  [P^T P | P^T Yt] = Q[:, :NP]^T Q is
 // a tall-skinny product over the m rows, summed in parts over row chunks
-// that a later launch adds in a fixed order, with the identity.  For NP <= 64
-// one launch builds each chunk of Q in LDS and multiplies it there
-// (k_red_pg); for NP = 128 Q goes through memory: k_red_prep writes it, and
-// each k_red_gemm workgroup takes one chunk of KC rows and one TS x TS output
-// tile (the upper tiles of the symmetric left half, every tile of the right
-// half).
+// that a later launch adds in a fixed order, with the identity.  Q is built in
+// LDS, 32 rows at a time, and multiplied there: by one workgroup per 32 rows
+// (k_red_pg) while N <= 64 and those are at most 256, else by 256 persistent
+// workgroups that add their chunks up (k_red_stream).
 // ---------------------------------------------------------------------------
 
 template <int NP> struct RedCfg {
   static constexpr int QW = 2 * NP;
-  static constexpr int TS = NP >= 64 ? 64 : 32;   // output tile
-  static constexpr int MB = TS / 32;              // 16x16 MFMA blocks per wave and direction
-  static constexpr int TT = NP / TS;              // tiles across the left half
-  static constexpr int NTG = TT * (TT + 1) / 2;   // upper tiles of the left half
-  static constexpr int NTILE = NTG + TT * TT;
   static constexpr int LPR = NP / 4;              // prep: lanes per row, 4 columns each
   static constexpr int RPB = kBlock / LPR;        // prep: rows per workgroup
 };
-
-// Row i of Q from X_f, idx, w, y, r and E (one group of NP/4 lanes per row).
-// Every workgroup writes its error word errw[blockIdx.x] (2: an index out of
-// range, else 0), so no word needs clearing beforehand.  The grid is
-// mpad / RPB workgroups.  SEN: the sEnKF's row scaling (see k_red_gram).
-template <typename T, int NP, bool SEN>
-__global__ __launch_bounds__(kBlock) void k_red_prep(int n, int m, int N, int k, const T* Xf,
-                                                     const int32_t* idx, const T* hw, const T* y,
-                                                     const T* rdiag, const T* eps, T* Q,
-                                                     int* errw) {
-  using C = RedCfg<NP>;
-  __shared__ int bad;
-  const int tid = threadIdx.x, q = tid % C::LPR;
-  const int i = blockIdx.x * C::RPB + tid / C::LPR;
-  const bool live = i < m;
-  if (tid == 0) bad = 0;
-  __syncthreads();
-  // the row's own inputs load alongside the gather
-  double yv = 0.0, rv = 1.0, ev[4] = {0.0, 0.0, 0.0, 0.0};
-  if (live) {
-    yv = (double)y[i];
-    rv = (double)rdiag[i];
-    if (eps) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (4 * q + u < N) ev[u] = (double)eps[(size_t)i * N + 4 * q + u];
-    }
-  }
-  // the entries of the operator row four at a time: their indices and weights
-  // first, then every X_f load (an index out of range reads row 0 with weight
-  // 0), summed in the order of t
-  double h[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int t0 = 0; t0 < k; t0 += 4) {
-    int c[4];
-    double wt[4];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int t = t0 + v;
-      c[v] = 0;
-      wt[v] = 0.0;
-      if (live && t < k) {
-        const int cx = idx[(size_t)i * k + t];
-        if ((unsigned)cx < (unsigned)n) {
-          c[v] = cx;
-          wt[v] = (double)hw[(size_t)i * k + t];
-        } else if (q == 0) {
-          atomicOr(&bad, 2);
-        }
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const T* xr = Xf + (size_t)c[v] * N;
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (4 * q + u < N) h[u] += wt[v] * (double)xr[4 * q + u];
-    }
-  }
-  // every lane takes part in the group sum; rows past m carry zeros
-  const double zb = group_sum<C::LPR>((h[0] + h[1]) + (h[2] + h[3])) / N;
-  __syncthreads();
-  if (tid == 0) errw[blockIdx.x] = bad;
-  double l2 = (double)(N - 1) * rv;
-  if constexpr (SEN) {
-    double ss = 0.0;
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-      if (4 * q + u < N) ss += (h[u] - zb) * (h[u] - zb);
-    l2 += group_sum<C::LPR>(ss);
-  }
-  const double l = sqrt(l2), yz = yv - zb;
-  T* qr = Q + (size_t)i * C::QW;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int j = 4 * q + u;
-    double pm = 0.0, yt = 0.0;
-    if (live && j < N) {
-      pm = (h[u] - zb) / l;
-      yt = (yz + ev[u] - (SEN ? h[u] - zb : 0.0)) / l;
-    }
-    qr[j] = (T)pm;
-    qr[NP + j] = (T)yt;
-  }
-}
 
 // Gather and product in one launch for NP <= 64.  Workgroup s builds rows
 // s KC .. s KC + KC - 1 of Q in LDS (zero past m), stored by column (a run of
 // KC rows per column, padded to spread the banks), then forms its part of
 // Q[:, :NP]^T Q on the MFMA: each wave a quarter of the NP x 2NP output, the
 // summation over the chunk's rows split into four runs of KC/4, one per lane
-// group (the same bijection for both operands).  errw[s] as in k_red_prep.
-// SEN: the sEnKF's row scaling, and only the right half Q[:, :NP]^T Q[:, NP:]
-// (each wave a quarter of it).
+// group (the same bijection for both operands).  Every workgroup writes its
+// error word errw[s] (2: an index out of range, else 0), so no word needs
+// clearing beforehand.
+// SEN: the sEnKF's row scaling, l_i^2 = ||s_i||^2 + (N-1) r_i (the i-th diagonal
+// entry of Zhat Zhat^T + (N-1) R), Yt = (Y - HX) / l, and only the right half
+// Q[:, :NP]^T Q[:, NP:] (each wave a quarter of it).
 constexpr int kRedFusedRows = 32;  // KC of the fused launch
 
 template <typename T, int NP, bool SEN>
@@ -679,76 +593,297 @@ __global__ __launch_bounds__(kBlock) void k_red_pg(int n, int m, int N, int k, c
         out[(size_t)(a0 + 16 * x + frag_row<T>(lk, i)) * C::QW + b0 + 16 * z + lr] = acc[x][z][i];
 }
 
-// part[s] (NP x 2NP, tile entries only) = Q[rows of chunk s, :NP]^T Q[rows of chunk s, :].
-// Grid (NTILE - t0, S), tile t0 + blockIdx.x (t0 = NTG: the right half only); four waves per tile, each a (TS/2) x (TS/2) quarter of
-// MB x MB MFMA blocks.  The next 32 rows load while the current ones multiply.
-template <typename T, int NP>
-__global__ __launch_bounds__(kBlock) void k_red_gemm(int KC, int mpad, int t0, const T* Q,
-                                                     T* part) {
-  using C = RedCfg<NP>;
-  using V = typename Vec4<T>::type;
-  constexpr int MB = C::MB, HS = C::TS / 2;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
-  int t = blockIdx.x + t0, ta = 0, tb;
-  if (t < C::NTG) {
-    while (t >= C::TT - ta) t -= C::TT - ta++;
-    tb = ta + t;
-  } else {
-    t -= C::NTG;
-    ta = t / C::TT;
-    tb = C::TT + t % C::TT;
-  }
-  const int ca = ta * C::TS + (wv >> 1) * HS + lr, cb = tb * C::TS + (wv & 1) * HS + lr;
-  const int r0 = blockIdx.y * KC, r1 = min(mpad, r0 + KC);
-  V acc[MB][MB];
-#pragma unroll
-  for (int x = 0; x < MB; ++x)
-#pragma unroll
-    for (int z = 0; z < MB; ++z) acc[x][z] = V{0, 0, 0, 0};
-  T an[8][MB], bn[8][MB];
-  auto load = [&](int r) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const T* row = Q + (size_t)(r + 4 * u + lk) * C::QW;
-#pragma unroll
-      for (int x = 0; x < MB; ++x) {
-        an[u][x] = row[ca + 16 * x];
-        bn[u][x] = row[cb + 16 * x];
-      }
-    }
-  };
-  load(r0);
-  for (int r = r0; r < r1; r += 32) {
-    T ac[8][MB], bc[8][MB];
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int x = 0; x < MB; ++x) {
-        ac[u][x] = an[u][x];
-        bc[u][x] = bn[u][x];
-      }
-    if (r + 32 < r1) load(r + 32);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int x = 0; x < MB; ++x)
-#pragma unroll
-        for (int z = 0; z < MB; ++z) acc[x][z] = mfma4(ac[u][x], bc[u][z], acc[x][z]);
-  }
-  T* out = part + (size_t)blockIdx.y * NP * C::QW;
-#pragma unroll
-  for (int x = 0; x < MB; ++x)
-#pragma unroll
-    for (int z = 0; z < MB; ++z)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        out[(size_t)(ca - lr + 16 * x + frag_row<T>(lk, i)) * C::QW + cb + 16 * z] = acc[x][z][i];
+// Gather and product in one persistent launch (TN = N / 16 rounded up), so that
+// neither Q nor a part per 32 rows goes to memory.  Workgroup s takes the chunks s,
+// s + gridDim.x, .. of 32 observation rows: it builds a chunk of Q in one of
+// two LDS buffers, stored by column as in k_red_pg, and multiplies it there;
+// each wave keeps its share of the output's 16 x 16 tiles (the upper tiles of
+// the symmetric left half, every tile of the right half) in accumulators until
+// the last chunk.  A chunk's indices are requested two chunks ahead and its
+// rows one chunk ahead, under the previous chunk's products.  Thread q of a
+// row takes the members q, q + 32, .. (coalesced reads; its LDS stores fall on
+// distinct banks).  part[s][tile][16][16]; errw and SEN (right half only) as in
+// k_red_pg.
+// Bound: the MFMA in FP64, the gather's latency in FP32.  At m = 10^5, N =
+// 100 in FP64 the two launches this replaces, with 205 MB of Q between them,
+// took 119 + 171 us, this one 119 us; at m = 16384, N = 128, k = 4 in FP32 (the
+// right half) 20 + 18 us and 23 us.  (Waves that gather while others multiply,
+// or the two waves of a SIMD in opposite order, ran out of registers.)
+constexpr int kRsRows = 32, kRsThreads = 512, kRsWaves = kRsThreads / 64;
+constexpr int kRsGroups = 256;  // one workgroup per CU
+
+// Past N = 64 always; below, once there are more chunks than workgroups, where
+// a part per chunk costs more than it spreads.
+inline bool red_streamed(int m, int N) {
+  return N > 64 || (m + kRsRows - 1) / kRsRows > kRsGroups;
+}
+// TN at N (as launch_red_stream chooses): two at least.
+inline int red_stream_tiles(int N) { return N <= 32 ? 2 : (N + 15) / 16; }
+
+template <int TN, bool SEN>
+struct RsCfg {
+  static constexpr int NTL = SEN ? 0 : TN * (TN + 1) / 2;  // left tiles
+  static constexpr int NT = NTL + TN * TN;
+  static constexpr int TPW = (NT + kRsWaves - 1) / kRsWaves;  // tiles per wave
+};
+template <typename T, int TN>
+constexpr size_t red_stream_lds() {
+  return sizeof(T) * 2 * (size_t)(32 * TN) * (kRsRows + 16 / sizeof(T));
 }
 
-// G = I + sum_s part_s[:, :NP] and B = I + sum_s part_s[:, NP:], restricted
-// to N x N (I scaled by dadd: 0 for the sEnKF, which passes NR = 0 and so
-// forms B only); a left-half entry below the diagonal tiles is read from its
-// mirror.  Eight lanes share an output: lane q adds the parts q, q + 8, ...
+template <typename T, int TN, bool SEN>
+__global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, int k, int nch,
+                                                           const T* Xf, const int32_t* idx,
+                                                           const T* hw, const T* y,
+                                                           const T* rdiag, const T* eps, T* part,
+                                                           int* errw) {
+  using C = RsCfg<TN, SEN>;
+  using V = typename Vec4<T>::type;
+  constexpr int KQ = kRsRows / 4, LQ = kRsRows + 16 / (int)sizeof(T), BUF = 32 * TN * LQ;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  T* qt = (T*)smem_raw;  // two buffers of 32 TN columns (P, then Yt) of LQ
+  __shared__ int bad;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  if (tid == 0) bad = 0;
+  __syncthreads();
+  // ---- the chunk's rows ----
+  // The first TB entries of an operator row travel ahead; the rest (k > TB) are
+  // read in finish().
+  constexpr int RPB = kRsThreads / 32, PASS = kRsRows / RPB;  // rows at once, rows per thread
+  constexpr int TB = sizeof(T) == 4 ? 4 : 2;
+  const int q = tid & 31, rw = tid >> 5;
+  int ci[PASS][TB];  // indices (and weights wn) of the next rows
+  T wn[PASS][TB], wc[PASS][TB], xv[PASS][TB][4], ev[PASS][4], yv[PASS], rv[PASS];
+      auto load_idx = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < PASS; ++u) {
+          const int i = ch * kRsRows + u * RPB + rw;
+#pragma unroll
+          for (int t = 0; t < TB; ++t) {
+            const bool on = i < m && t < k;
+            ci[u][t] = on ? idx[(size_t)i * k + t] : 0;
+            wn[u][t] = on ? hw[(size_t)i * k + t] : (T)0;
+          }
+        }
+      };
+      auto load_rows = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < PASS; ++u) {
+          const int i = ch * kRsRows + u * RPB + rw;
+          const bool live = i < m;
+          yv[u] = live ? y[i] : (T)0;
+          rv[u] = live ? rdiag[i] : (T)1;
+#pragma unroll
+          for (int c = 0; c < 4; ++c)
+            ev[u][c] = (live && eps && q + 32 * c < N) ? eps[(size_t)i * N + q + 32 * c] : (T)0;
+#pragma unroll
+          for (int t = 0; t < TB; ++t) {
+            wc[u][t] = wn[u][t];
+            if (t < k) {
+              int cx = ci[u][t];
+              if ((unsigned)cx >= (unsigned)n) {  // (rows past m hold index 0, weight 0)
+                if (q == 0) atomicOr(&bad, 2);
+                cx = 0;
+                wc[u][t] = (T)0;
+              }
+#pragma unroll
+              for (int c = 0; c < 4; ++c)
+                xv[u][t][c] = q + 32 * c < N ? Xf[(size_t)cx * N + q + 32 * c] : (T)0;
+            }
+          }
+        }
+      };
+      auto finish = [&](int ch, T* buf) __attribute__((always_inline)) {
+        double h[PASS][4];
+#pragma unroll
+        for (int u = 0; u < PASS; ++u)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            h[u][c] = 0.0;
+#pragma unroll
+            for (int t = 0; t < TB; ++t)
+              if (t < k) h[u][c] += (double)wc[u][t] * (double)xv[u][t][c];
+          }
+        for (int t = TB; t < k; ++t)
+#pragma unroll
+          for (int u = 0; u < PASS; ++u) {
+            const int i = ch * kRsRows + u * RPB + rw;
+            if (i >= m) continue;
+            const int cx = idx[(size_t)i * k + t];
+            if ((unsigned)cx >= (unsigned)n) {
+              if (q == 0) atomicOr(&bad, 2);
+              continue;
+            }
+            const double w = (double)hw[(size_t)i * k + t];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (q + 32 * c < N) h[u][c] += w * (double)Xf[(size_t)cx * N + q + 32 * c];
+          }
+#pragma unroll
+        for (int u = 0; u < PASS; ++u) {
+          const int rr = u * RPB + rw;
+          const bool live = ch * kRsRows + rr < m;
+          const double zb = group_sum<32>((h[u][0] + h[u][1]) + (h[u][2] + h[u][3])) / N;
+          double l2 = (double)(N - 1) * (double)rv[u];
+          if constexpr (SEN) {
+            double ss = 0.0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+              if (q + 32 * c < N) ss += (h[u][c] - zb) * (h[u][c] - zb);
+            l2 += group_sum<32>(ss);
+          }
+          const double l = sqrt(l2), yz = (double)yv[u] - zb;
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const int j = q + 32 * c;
+            double pm = 0.0, yt = 0.0;
+            if (live && j < N) {
+              pm = (h[u][c] - zb) / l;
+              yt = (yz + (double)ev[u][c] - (SEN ? h[u][c] - zb : 0.0)) / l;
+            }
+            if (j < 16 * TN) {
+              buf[j * LQ + rr] = (T)pm;
+              buf[(16 * TN + j) * LQ + rr] = (T)yt;
+            }
+          }
+        }
+      };
+
+  // ---- this wave's tiles (LDS offsets of their columns) ----
+  const int lr = lane & 15, lk = lane >> 4;
+  const int t0 = __builtin_amdgcn_readfirstlane(wv) * C::TPW;
+  int ao[C::TPW], bo[C::TPW];
+#pragma unroll
+  for (int i = 0; i < C::TPW; ++i) {
+    int t = t0 + i, ta = 0;
+    if (t < C::NTL) {
+#pragma unroll
+      for (int z = 0; z < TN; ++z)  // row ta of the upper triangle starts at ta TN - ta (ta - 1) / 2
+        if (t >= (z + 1) * TN - (z + 1) * z / 2) ta = z + 1;
+      bo[i] = 16 * (t - ta * TN + ta * (ta - 1) / 2 + ta) * LQ;
+      ao[i] = 16 * ta * LQ;
+    } else {
+      t -= C::NTL;
+      ao[i] = 16 * (t / TN) * LQ;
+      bo[i] = 16 * (TN + t % TN) * LQ;
+    }
+  }
+  V acc[C::TPW];
+#pragma unroll
+  for (int i = 0; i < C::TPW; ++i) acc[i] = V{0, 0, 0, 0};
+  const int G = gridDim.x;
+  int b = 0, ch = blockIdx.x;
+  load_idx(ch);
+  load_rows(ch);
+  load_idx(ch + G);
+  for (; ch < nch; ch += G, b ^= 1) {
+    // (a wave may still be multiplying the other buffer)
+    finish(ch, qt + b * BUF);
+    load_rows(ch + G);
+    load_idx(ch + 2 * G);
+    __syncthreads();
+    const T* base = qt + b * BUF + lr * LQ + lk * KQ;
+    T av[KQ];
+#pragma unroll
+    for (int i = 0; i < C::TPW; ++i) {
+      if (t0 + i < C::NT) {
+        if (i == 0 || ao[i] != ao[i - 1]) vload<KQ>(base + ao[i], av);
+        T bv[KQ];
+        vload<KQ>(base + bo[i], bv);
+#pragma unroll
+        for (int u = 0; u < KQ; ++u) acc[i] = mfma4(av[u], bv[u], acc[i]);
+      }
+      __builtin_amdgcn_sched_barrier(0);  // one tile's operands at a time
+    }
+  }
+  __syncthreads();
+  if (tid == 0) errw[blockIdx.x] = bad;
+  T* out = part + ((size_t)blockIdx.x * C::NT + t0) * 256;
+#pragma unroll
+  for (int i = 0; i < C::TPW; ++i)
+    if (t0 + i < C::NT)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) out[i * 256 + frag_row<T>(lk, v) * 16 + lr] = acc[i][v];
+}
+
+// The sums of k_red_stream's parts: G (rows of stride LG, both triangles;
+// only N x N is written) and B, I added, or, SEN, the update's Wt[b][a] (NP x
+// NP, zero outside N x N; zeros to iters0).  A workgroup takes 32 threads of
+// 16 consecutive bytes of a tile, eight times: thread row sub adds the parts
+// sub, sub + 8, .. in order, then the eight are added in order.
+template <typename T, bool SEN>
+__global__ __launch_bounds__(kBlock) void k_red_sum_tiles(int N, int TN, int LG, int S,
+                                                          const T* part, double* Gp, double* B,
+                                                          T* Wt, int NP, const int* errw, int nerr,
+                                                          int* err, int* iters0) {
+  constexpr int VU = 16 / (int)sizeof(T);
+  __shared__ double red[8][32][VU];
+  const int tid = threadIdx.x, x = tid & 31, sub = tid >> 5;
+  if (blockIdx.x == 0) {
+    if (SEN && iters0)
+      for (int e = tid; e < N; e += kBlock) iters0[e] = 0;
+    __shared__ int flags;
+    if (tid == 0) flags = 0;
+    __syncthreads();
+    int f = 0;
+    for (int e = tid; e < nerr; e += kBlock) f |= errw[e];
+    if (f) atomicOr(&flags, f);
+    __syncthreads();
+    if (tid == 0) *err = flags;
+  }
+  if (SEN)  // the padding past the tiles
+    for (int e = blockIdx.x * kBlock + tid; e < NP * NP; e += gridDim.x * kBlock)
+      if (e / NP >= 16 * TN || e % NP >= 16 * TN) Wt[e] = (T)0;
+  const int ntl = SEN ? 0 : TN * (TN + 1) / 2, nt = ntl + TN * TN;
+  const int e0 = (blockIdx.x * 32 + x) * VU;  // first element (grid: nt * 256 / (32 VU))
+  int t = e0 / 256, ti = 0, tj;
+  const T* src = part + e0;
+  double acc[VU];
+#pragma unroll
+  for (int v = 0; v < VU; ++v) acc[v] = 0.0;
+#pragma unroll 8
+  for (int s = sub; s < S; s += 8) {
+    T v[VU];
+    vload<VU>(src + (size_t)s * nt * 256, v);
+#pragma unroll
+    for (int u = 0; u < VU; ++u) acc[u] += (double)v[u];
+  }
+#pragma unroll
+  for (int v = 0; v < VU; ++v) red[sub][x][v] = acc[v];
+  __syncthreads();
+  if (sub != 0) return;
+  for (int u = 1; u < 8; ++u)
+#pragma unroll
+    for (int v = 0; v < VU; ++v) acc[v] += red[u][x][v];
+  const bool right = t >= ntl;
+  if (right) {
+    t -= ntl;
+    ti = t / TN;
+    tj = t % TN;
+  } else {
+    while (t >= TN - ti) t -= TN - ti++;
+    tj = ti + t;
+  }
+  const int a = 16 * ti + (e0 % 256) / 16, b0 = 16 * tj + e0 % 16;
+#pragma unroll
+  for (int v = 0; v < VU; ++v) {
+    const int b = b0 + v;
+    const double o = acc[v] + (a == b ? 1.0 : 0.0);
+    if (SEN) {
+      Wt[(size_t)b * NP + a] = (T)((a < N && b < N) ? acc[v] : 0.0);
+    } else if (a < N && b < N) {
+      if (right) {
+        B[(size_t)a * N + b] = o;
+      } else {
+        Gp[(size_t)a * LG + b] = o;
+        if (ti != tj) Gp[(size_t)b * LG + a] = o;
+      }
+    }
+  }
+}
+
+// G = I + sum_s part_s[:, :NP] and B = I + sum_s part_s[:, NP:] of k_red_pg's
+// parts, restricted to N x N.  Eight lanes share an output: lane q adds the parts q, q + 8, ...
 // in order, then a fixed lane tree adds the eight.  G is written as the
 // solve keeps it in LDS: NR rows of stride LG, zero outside N x N; B is
 // N x N.  Workgroup 0 also folds the gather's error
@@ -756,8 +891,7 @@ __global__ __launch_bounds__(kBlock) void k_red_gemm(int KC, int mpad, int t0, c
 template <typename T, int NP>
 __global__ __launch_bounds__(kBlock) void k_red_sum2(int N, int NR, int LG, int S,
                                                      const T* part, double* Gp, double* B,
-                                                     const int* errw, int nerr, int* err,
-                                                     double dadd) {
+                                                     const int* errw, int nerr, int* err) {
   using C = RedCfg<NP>;
   const int tid = threadIdx.x, q = tid & 7;
   if (blockIdx.x == 0) {
@@ -786,15 +920,14 @@ __global__ __launch_bounds__(kBlock) void k_red_sum2(int N, int NR, int LG, int 
   }
   double acc = 0.0;
   if (live) {
-    const bool mirror = !right && a / C::TS > b / C::TS;
-    const T* src = part + (size_t)(mirror ? b : a) * C::QW + (right ? NP : 0) + (mirror ? a : b);
+    const T* src = part + (size_t)a * C::QW + (right ? NP : 0) + b;
     const size_t stride = (size_t)NP * C::QW;
 #pragma unroll 4
     for (int s = q; s < S; s += 8) acc += (double)src[s * stride];
   }
   acc = group_sum<8>(acc);
   if (q == 0 && o < total) {
-    if (live && a == b) acc += dadd;
+    if (live && a == b) acc += 1.0;
     if (right)
       B[o - ng] = acc;
     else
@@ -841,8 +974,8 @@ __global__ __launch_bounds__(kBlock) void k_senkf_sum(int N, int S, const T* par
 
 // CGD-EnKF-Reduced solve for N <= 64 RPL: textbook CG on G w = b_j from
 // w = 0 (Lemma 1: at most N steps in exact arithmetic), one workgroup per
-// column.  G comes as the sum launch lays it out (LG = 64 RPL rows of stride
-// LG, zero outside N x N); each wave keeps a quarter of its rows in
+// column.  G comes as the sum launch lays it out (stride LG = 64 RPL; only N x
+// N is read); each wave keeps a quarter of its rows in
 // registers (reading G from LDS every step cost 0.43 us a step at N = 128).
 // Each wave carries the whole recurrence (lane l holds rows l + 64 u of w,
 // r, p, q), the same values in every wave, but forms only a quarter of
@@ -874,7 +1007,10 @@ __global__ __launch_bounds__(kBlock) void k_small_cg_w(int N, int NP, const doub
 #pragma unroll
   for (int t = 0; t < QR; ++t)
 #pragma unroll
-    for (int u = 0; u < RPL; ++u) gr[t][u] = Gp[(size_t)(wv * QR + t) * LG + lane + 64 * u];
+    for (int u = 0; u < RPL; ++u) {
+      const int l = wv * QR + t, i = lane + 64 * u;
+      gr[t][u] = l < N && i < N ? Gp[(size_t)l * LG + i] : 0.0;
+    }
   double x[RPL], r[RPL], p[RPL];
   double part = 0.0;
 #pragma unroll
@@ -1366,28 +1502,23 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
 
 int reduced_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
   if (N < 2 || N > 128 || m < 1 || m > (1 << 30)) return 0;
-  const int np = N <= 32 ? 32 : N <= 64 ? 64 : 128;
-  if (np <= 64) {
-    // gather and product fused: chunks of kRedFusedRows rows, no Q in memory
-    *NP = np;
-    *KC = kRedFusedRows;
-    *S = (m + kRedFusedRows - 1) / kRedFusedRows;
-    *mpad = *S * kRedFusedRows;
-    return 1;
-  }
-  const int tiles = np == 32 ? RedCfg<32>::NTILE : np == 64 ? RedCfg<64>::NTILE : RedCfg<128>::NTILE;
-  const long mp = ((long)m + 31) / 32 * 32, blocks = mp / 32;
-  // about 512 workgroups, chunks of at least 64 rows
-  long sc = (512 + tiles - 1) / tiles;
-  const long smax = (mp + 63) / 64;
-  if (sc > smax) sc = smax;
-  if (sc < 1) sc = 1;
-  const long kc = (blocks + sc - 1) / sc * 32;
-  *NP = np;
-  *mpad = (int)mp;
-  *KC = (int)kc;
-  *S = (int)((mp + kc - 1) / kc);
+  static_assert(kRedFusedRows == kRsRows, "one chunk height");
+  const int nch = (m + kRsRows - 1) / kRsRows;
+  *NP = N <= 32 ? 32 : N <= 64 ? 64 : 128;
+  *KC = kRsRows;
+  *S = red_streamed(m, N) && nch > kRsGroups ? kRsGroups : nch;
+  *mpad = nch * kRsRows;
   return 1;
+}
+
+// 16 x 16 tiles of the product a part holds: all of NP x 2NP from k_red_pg.
+size_t reduced_part_elems(int m, int N) {
+  if (!red_streamed(m, N)) {
+    const size_t np = N <= 32 ? 32 : 64;
+    return np * 2 * np;
+  }
+  const size_t tn = red_stream_tiles(N);
+  return (tn * (tn + 1) / 2 + tn * tn) * 256;
 }
 
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
@@ -1449,14 +1580,41 @@ hipError_t launch_red_update_np(int n, int N, const T* Xf, T* Xa, const T* Wt, h
   return launch_red_update<T, NP, 16>(n, N, Xf, Xa, Wt, s);
 }
 
+template <typename T, int TN, bool SEN>
+hipError_t launch_red_stream_tn(int n, int m, int N, int k, int S, const T* Xg, const int32_t* idx,
+                                const T* hw, const T* y, const T* rdiag, const T* eps, T* part,
+                                int* errw, hipStream_t s) {
+  constexpr size_t lds = red_stream_lds<T, TN>();
+  const hipError_t e = hipFuncSetAttribute((const void*)k_red_stream<T, TN, SEN>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_red_stream<T, TN, SEN>), dim3(S), dim3(kRsThreads), lds, s, n, m, N, k,
+                     (m + kRsRows - 1) / kRsRows, Xg, idx, hw, y, rdiag, eps, part, errw);
+  return hipGetLastError();
+}
+template <typename T, bool SEN>
+hipError_t launch_red_stream(int n, int m, int N, int k, int S, const T* Xg, const int32_t* idx,
+                             const T* hw, const T* y, const T* rdiag, const T* eps, T* part,
+                             int* errw, hipStream_t s) {
+  auto one = [&](auto tn) {
+    return launch_red_stream_tn<T, decltype(tn)::value, SEN>(n, m, N, k, S, Xg, idx, hw, y, rdiag,
+                                                             eps, part, errw, s);
+  };
+  if (N <= 32) return one(std::integral_constant<int, 2>{});
+  if (N <= 48) return one(std::integral_constant<int, 3>{});
+  if (N <= 64) return one(std::integral_constant<int, 4>{});
+  if (N <= 80) return one(std::integral_constant<int, 5>{});
+  if (N <= 96) return one(std::integral_constant<int, 6>{});
+  if (N <= 112) return one(std::integral_constant<int, 7>{});
+  return one(std::integral_constant<int, 8>{});
+}
+
 template <typename T, int NP>
 hipError_t launch_reduced_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, const T* Xg, int ng,
                                const int32_t* idx, const T* hw, const T* y, const T* rdiag,
                                const T* eps, double tol, int maxit, void* ws, const Layout& L,
                                int* iters_out, hipStream_t s) {
-  using C = RedCfg<NP>;
   unsigned char* base = (unsigned char*)ws;
-  T* Q = (T*)(base + L.rQ);
   T* part = (T*)(base + L.rpart);
   double* Gp = (double*)(base + L.rG);
   double* B = (double*)(base + L.rB);
@@ -1468,24 +1626,22 @@ hipError_t launch_reduced_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, c
   int* errw = (int*)(base + L.rerr);
   const int LG = NP < 64 ? 64 : NP, RPL = LG / 64, NR = LG;
   hipError_t e;
-  int nprep;
-  if constexpr (NP <= 64) {
-    nprep = L.rS;
+  if (red_streamed(m, N)) {
+    if ((e = launch_red_stream<T, false>(ng, m, N, k, L.rS, Xg, idx, hw, y, rdiag, eps, part, errw,
+                                         s)) != hipSuccess)
+      return e;
+    const int tn = red_stream_tiles(N), nt = tn * (tn + 1) / 2 + tn * tn;
+    hipLaunchKernelGGL((k_red_sum_tiles<T, false>), dim3(nt * 8 * sizeof(T) / 16), dim3(kBlock), 0,
+                       s, N, tn, LG, L.rS, (const T*)part, Gp, B, (T*)nullptr, NP,
+                       (const int*)errw, L.rS, err, (int*)nullptr);
+  } else if constexpr (NP <= 64) {
     hipLaunchKernelGGL((k_red_pg<T, NP, false>), dim3(L.rS), dim3(kBlock), 0, s, ng, m, N, k, Xg,
                        idx, hw, y, rdiag, eps, part, errw);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else {
-    nprep = L.rmpad / C::RPB;
-    hipLaunchKernelGGL((k_red_prep<T, NP, false>), dim3(nprep), dim3(kBlock), 0, s, ng, m, N, k,
-                       Xg, idx, hw, y, rdiag, eps, Q, errw);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_red_gemm<T, NP>), dim3(C::NTILE, L.rS), dim3(kBlock), 0, s, L.rKC,
-                       L.rmpad, 0, (const T*)Q, part);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int nsum = NR * LG + N * N, per = kBlock / 8;
+    hipLaunchKernelGGL((k_red_sum2<T, NP>), dim3((nsum + per - 1) / per), dim3(kBlock), 0, s, N,
+                       NR, LG, L.rS, (const T*)part, Gp, B, (const int*)errw, L.rS, err);
   }
-  const int nsum = NR * LG + N * N, per = kBlock / 8;
-  hipLaunchKernelGGL((k_red_sum2<T, NP>), dim3((nsum + per - 1) / per), dim3(kBlock), 0, s, N, NR,
-                     LG, L.rS, (const T*)part, Gp, B, (const int*)errw, nprep, err, 1.0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const size_t lds = sizeof(double) * (3 * (kBlock / 64) * (size_t)LG);
   if (RPL == 1) {
@@ -1583,31 +1739,28 @@ template <typename T, int NP>
 hipError_t launch_senkf_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, const int32_t* idx,
                              const T* hw, const T* y, const T* rdiag, const T* eps, void* ws,
                              const Layout& L, int* iters0, hipStream_t s) {
-  using C = RedCfg<NP>;
   unsigned char* base = (unsigned char*)ws;
-  T* Q = (T*)(base + L.rQ);
   T* part = (T*)(base + L.rpart);
   int* err = (int*)(base + L.err);
   int* errw = (int*)(base + L.rerr);
+  T* Wt = (T*)(base + L.rWt);
   hipError_t e;
-  int nprep;
-  if constexpr (NP <= 64) {
-    nprep = L.rS;
+  if (red_streamed(m, N)) {
+    if ((e = launch_red_stream<T, true>(n, m, N, k, L.rS, Xf, idx, hw, y, rdiag, eps, part, errw,
+                                        s)) != hipSuccess)
+      return e;
+    const int tn = red_stream_tiles(N);
+    hipLaunchKernelGGL((k_red_sum_tiles<T, true>), dim3(tn * tn * 8 * sizeof(T) / 16), dim3(kBlock),
+                       0, s, N, tn, 0, L.rS, (const T*)part, (double*)nullptr, (double*)nullptr, Wt,
+                       NP, (const int*)errw, L.rS, err, iters0);
+  } else if constexpr (NP <= 64) {
     hipLaunchKernelGGL((k_red_pg<T, NP, true>), dim3(L.rS), dim3(kBlock), 0, s, n, m, N, k, Xf,
                        idx, hw, y, rdiag, eps, part, errw);
-  } else {
-    nprep = L.rmpad / C::RPB;
-    hipLaunchKernelGGL((k_red_prep<T, NP, true>), dim3(nprep), dim3(kBlock), 0, s, n, m, N, k, Xf,
-                       idx, hw, y, rdiag, eps, Q, errw);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL((k_red_gemm<T, NP>), dim3(C::NTILE - C::NTG, L.rS), dim3(kBlock), 0, s,
-                       L.rKC, L.rmpad, C::NTG, (const T*)Q, part);
+    const int per = kBlock / 8;
+    hipLaunchKernelGGL((k_senkf_sum<T, NP>), dim3((NP * NP + per - 1) / per), dim3(kBlock), 0, s,
+                       N, L.rS, (const T*)part, Wt, (const int*)errw, L.rS, err, iters0);
   }
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int per = kBlock / 8;
-  T* Wt = (T*)(base + L.rWt);
-  hipLaunchKernelGGL((k_senkf_sum<T, NP>), dim3((NP * NP + per - 1) / per), dim3(kBlock), 0, s,
-                     N, L.rS, (const T*)part, Wt, (const int*)errw, nprep, err, iters0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_red_update_np<T, NP>(n, N, Xf, Xa, Wt, s);
 }
