@@ -51,68 +51,119 @@ constexpr int taps_pad() { return CIN == 16 ? 6 : 5; }
 // output of channel 0 only (last layer), MODE 2 backward over the data:
 // no bias, output multiplied by [mask > 0] (ReLU derivative of the layer
 // input), BF16 out.
+//
+// Persistent: a workgroup takes every gridDim.x-th tile of kTile positions and
+// keeps the whole weight tensor in its waves' registers (KS x TO fragments);
+// the next tile's input rows load while the current ones multiply, into the
+// other of two LDS buffers.  The weights are the MFMA's A operand, so a lane
+// ends with channels of one position; row m of output tile `to` is channel
+// 16 (m / 4) + 4 to + m % 4 (64 channels), which gives it 16 consecutive ones
+// (32-byte stores).  The sums are those of the plain order: every product's k
+// runs as before.
+// Bound: memory (64 -> 64 channels at 64 x 2048 positions: 34 MB forward, 50 MB
+// backward).  A workgroup per tile, staging 41 KiB of weights each time, took
+// 24 and 33 us; this 19 and 21 us.
 // ---------------------------------------------------------------------------
+constexpr int kConvGroups = 512;  // two workgroups per CU
+
 template <int CIN, int COUT, int MODE>
-__global__ __launch_bounds__(256) void k_conv(int M, const __bf16* __restrict__ in,
-                                              const __bf16* __restrict__ W,
-                                              const float* __restrict__ bias,
-                                              const __bf16* __restrict__ mask, void* out) {
+__global__ __launch_bounds__(256, 2) void k_conv(int M, int ntile, int tpr,
+                                                 const __bf16* __restrict__ in,
+                                                 const __bf16* __restrict__ W,
+                                                 const float* __restrict__ bias,
+                                                 const __bf16* __restrict__ mask, void* out) {
   constexpr int TP = taps_pad<CIN>();
-  constexpr int K = TP * CIN;              // multiple of 32
-  constexpr int ROWS = kTile + TP - 1;     // staged input rows
-  constexpr int LDX = CIN + 8;             // padded row strides (16-byte aligned)
-  constexpr int LDW = K + 8;
-  constexpr int TO = COUT / 16, NT = 4 * TO, TPW = NT / 4;
-  __shared__ __align__(16) __bf16 xs[ROWS * LDX];
-  __shared__ __align__(16) __bf16 ws[COUT * LDW];
+  constexpr int K = TP * CIN, KS = K / 32;  // K: a multiple of 32
+  constexpr int ROWS = kTile + TP - 1;      // staged input rows
+  constexpr int LDX = CIN + 8;              // padded row stride (16-byte aligned)
+  constexpr int TO = COUT / 16, CPR = CIN / 8, NCH = ROWS * CPR, NLD = (NCH + 255) / 256;
+  __shared__ __align__(16) __bf16 xs[2][ROWS * LDX];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.y, i0 = blockIdx.x * kTile;
-  const __bf16* inb = in + (size_t)b * M * CIN;
-  // stage input rows i0-2 .. i0+kTile+TP-4 (circular), 8 channels per copy
-  for (int e = tid; e < ROWS * (CIN / 8); e += 256) {
-    const int r = e / (CIN / 8), c8 = e - r * (CIN / 8);
-    int pos = i0 - 2 + r;
-    pos %= M;
-    if (pos < 0) pos += M;
-    *reinterpret_cast<bf16x8*>(xs + r * LDX + c8 * 8) =
-        *reinterpret_cast<const bf16x8*>(inb + (size_t)pos * CIN + c8 * 8);
-  }
-  for (int e = tid; e < COUT * (K / 8); e += 256) {
-    const int o = e / (K / 8), k8 = e - o * (K / 8);
-    *reinterpret_cast<bf16x8*>(ws + o * LDW + k8 * 8) =
-        *reinterpret_cast<const bf16x8*>(W + (size_t)o * K + k8 * 8);
-  }
-  __syncthreads();
+  // channel of row m of output tile to, and this lane's first channel
+  auto chan = [](int to, int m) { return TO == 4 ? 16 * (m >> 2) + 4 * to + (m & 3) : 16 * to + m; };
+  bf16x8 wf[KS][TO];
 #pragma unroll
-  for (int s = 0; s < TPW; ++s) {
-    const int tile = wv + 4 * s;
-    const int ti = tile / TO, to = tile - ti * TO;
-    f32x4 acc = {0, 0, 0, 0};
+  for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-    for (int ks = 0; ks < K / 32; ++ks) {
-      const int k0 = ks * 32 + 8 * lg;
-      const int t = k0 / CIN, c = k0 - t * CIN;
-      const bf16x8 a = *reinterpret_cast<const bf16x8*>(xs + (ti * 16 + lr + t) * LDX + c);
-      const bf16x8 w = *reinterpret_cast<const bf16x8*>(ws + (to * 16 + lr) * LDW + k0);
-      acc = mfma_bf16(a, w, acc);
-    }
-    const int ch = to * 16 + lr;
+    for (int to = 0; to < TO; ++to)
+      wf[ks][to] = *reinterpret_cast<const bf16x8*>(W + (size_t)chan(to, lr) * K + ks * 32 + 8 * lg);
+  bf16x8 xr[NLD];
+  // input rows i0-2 .. i0+kTile+TP-4 of a tile (circular), 8 channels per copy
+  auto fetch = [&](int tile) {
+    const int b = tile / tpr, i0 = (tile - b * tpr) * kTile;
+    const __bf16* inb = in + (size_t)b * M * CIN;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int pos = i0 + ti * 16 + 4 * lg + q;
-      if (pos >= M) continue;
-      float v = acc[q];
-      if constexpr (MODE == 0) {
-        v += bias[ch];
-        v = v > 0.f ? v : 0.f;
-        ((__bf16*)out)[((size_t)b * M + pos) * COUT + ch] = (__bf16)v;
-      } else if constexpr (MODE == 1) {
-        if (ch == 0) ((float*)out)[(size_t)b * M + pos] = v + bias[0];
-      } else {
-        const float mk = (float)mask[((size_t)b * M + pos) * COUT + ch];
-        ((__bf16*)out)[((size_t)b * M + pos) * COUT + ch] = (__bf16)(mk > 0.f ? v : 0.f);
+    for (int u = 0; u < NLD; ++u) {
+      const int e = u * 256 + tid, r = e / CPR, c8 = e - r * CPR;
+      if (e < NCH) {
+        int pos = (i0 - 2 + r) % M;
+        if (pos < 0) pos += M;
+        xr[u] = *reinterpret_cast<const bf16x8*>(inb + (size_t)pos * CIN + c8 * 8);
       }
     }
+  };
+  auto put = [&](__bf16* x) {
+#pragma unroll
+    for (int u = 0; u < NLD; ++u) {
+      const int e = u * 256 + tid, r = e / CPR, c8 = e - r * CPR;
+      if (e < NCH) *reinterpret_cast<bf16x8*>(x + r * LDX + c8 * 8) = xr[u];
+    }
+  };
+  int tile = blockIdx.x, buf = 0;
+  fetch(tile);
+  put(xs[0]);
+  __syncthreads();
+  for (; tile < ntile; tile += gridDim.x, buf ^= 1) {
+    const int next = tile + gridDim.x;
+    const int b = tile / tpr, pos = (tile - b * tpr) * kTile + wv * 16 + lr;
+    const size_t at = ((size_t)b * M + pos) * COUT + (TO == 4 ? 16 * lg : 4 * lg);
+    bf16x8 mk[2];
+    if constexpr (MODE == 2) {
+      static_assert(MODE != 2 || TO == 4, "backward layers have 64 channels");
+      if (pos < M) {
+        mk[0] = *reinterpret_cast<const bf16x8*>(mask + at);
+        mk[1] = *reinterpret_cast<const bf16x8*>(mask + at + 8);
+      }
+    }
+    if (next < ntile) fetch(next);
+    f32x4 acc[TO];
+#pragma unroll
+    for (int to = 0; to < TO; ++to) acc[to] = f32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int k0 = ks * 32 + 8 * lg;
+      const int t = k0 / CIN, c = k0 - t * CIN;
+      const bf16x8 x =
+          *reinterpret_cast<const bf16x8*>(xs[buf] + (wv * 16 + lr + t) * LDX + c);
+#pragma unroll
+      for (int to = 0; to < TO; ++to) acc[to] = mfma_bf16(wf[ks][to], x, acc[to]);
+    }
+    if (pos < M) {
+      if constexpr (MODE == 1) {
+        if (lg == 0) ((float*)out)[(size_t)b * M + pos] = acc[0][0] + bias[0];  // channel 0
+      } else {
+        static_assert(MODE == 1 || TO == 4, "hidden layers have 64 channels");
+        bf16x8 o[2];
+#pragma unroll
+        for (int to = 0; to < TO; ++to)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int e = 4 * to + q;  // channel 16 lg + e
+            float v = acc[to][q];
+            if constexpr (MODE == 0) {
+              v += bias[16 * lg + e];
+              v = v > 0.f ? v : 0.f;
+            } else {
+              v = (float)mk[e / 8][e % 8] > 0.f ? v : 0.f;
+            }
+            o[e / 8][e % 8] = (__bf16)v;
+          }
+        *reinterpret_cast<bf16x8*>((__bf16*)out + at) = o[0];
+        *reinterpret_cast<bf16x8*>((__bf16*)out + at + 8) = o[1];
+      }
+    }
+    if (next < ntile) put(xs[buf ^ 1]);
+    __syncthreads();
   }
 }
 
@@ -383,25 +434,40 @@ __global__ void k_adam(int n, float* p, float* m, float* v, const float* g, floa
   p[e] -= lr * (mm / c1) / (sqrtf(vv / c2) + eps);
 }
 
-// Packed BF16 weights of one layer: forward Wf[o][t][c] (COUTP x TPF x CINP)
-// and backward-data Wb[c][t'][o] = W[o][c][4 - t'] (CINP x TPB x COUTP); FP32
-// bias padded to COUTP.
-__global__ void k_pack(int cin, int cout, int CINP, int COUTP, int TPF, int TPB, const float* w,
-                       const float* bias, __bf16* Wf, __bf16* Wb, float* biasp) {
+// Packed BF16 weights of every layer (blockIdx.y): forward Wf[o][t][c] (COUTP x
+// TPF x CINP) and backward-data Wb[c][t'][o] = W[o][c][4 - t'] (CINP x TPB x
+// COUTP); FP32 bias padded to COUTP.
+struct PackLayer {
+  int cin, cout, CINP, COUTP, TPF, TPB;
+  const float* w;
+  const float* bias;
+  __bf16* Wf;
+  __bf16* Wb;
+  float* biasp;
+};
+struct PackArgs {
+  PackLayer l[4];
+};
+__global__ void k_pack(PackArgs a) {
+  const PackLayer& L = a.l[blockIdx.y];
   const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  const int nf = COUTP * TPF * CINP, nb = CINP * TPB * COUTP;
+  const int nf = L.COUTP * L.TPF * L.CINP, nb = L.CINP * L.TPB * L.COUTP;
   if (e < nf) {
-    const int o = e / (TPF * CINP), r = e - o * TPF * CINP, t = r / CINP, c = r - t * CINP;
-    const float v = (o < cout && c < cin && t < 5) ? w[((size_t)o * cin + c) * 5 + t] : 0.f;
-    Wf[e] = (__bf16)v;
+    const int o = e / (L.TPF * L.CINP), r = e - o * L.TPF * L.CINP, t = r / L.CINP;
+    const int c = r - t * L.CINP;
+    const float v =
+        (o < L.cout && c < L.cin && t < 5) ? L.w[((size_t)o * L.cin + c) * 5 + t] : 0.f;
+    L.Wf[e] = (__bf16)v;
   } else if (e < nf + nb) {
     const int f = e - nf;
-    const int c = f / (TPB * COUTP), r = f - c * TPB * COUTP, t = r / COUTP, o = r - t * COUTP;
-    const float v = (o < cout && c < cin && t < 5) ? w[((size_t)o * cin + c) * 5 + (4 - t)] : 0.f;
-    Wb[f] = (__bf16)v;
-  } else if (e < nf + nb + COUTP) {
+    const int c = f / (L.TPB * L.COUTP), r = f - c * L.TPB * L.COUTP, t = r / L.COUTP;
+    const int o = r - t * L.COUTP;
+    const float v =
+        (o < L.cout && c < L.cin && t < 5) ? L.w[((size_t)o * L.cin + c) * 5 + (4 - t)] : 0.f;
+    L.Wb[f] = (__bf16)v;
+  } else if (e < nf + nb + L.COUTP) {
     const int o = e - nf - nb;
-    biasp[o] = o < cout ? bias[o] : 0.f;
+    L.biasp[o] = o < L.cout ? L.bias[o] : 0.f;
   }
 }
 
@@ -844,8 +910,9 @@ __global__ void k_z0(int m, int N, const float* out, const float* scale, float* 
 template <int CIN, int COUT, int MODE>
 hipError_t conv(int B, int M, const __bf16* in, const __bf16* W, const float* bias,
                 const __bf16* mask, void* out, hipStream_t s) {
-  hipLaunchKernelGGL((k_conv<CIN, COUT, MODE>), dim3((M + kTile - 1) / kTile, B), dim3(256), 0,
-                     s, M, in, W, bias, mask, out);
+  const int tpr = (M + kTile - 1) / kTile, ntile = B * tpr;
+  hipLaunchKernelGGL((k_conv<CIN, COUT, MODE>), dim3(ntile < kConvGroups ? ntile : kConvGroups),
+                     dim3(256), 0, s, M, ntile, tpr, in, W, bias, mask, out);
   return hipGetLastError();
 }
 
@@ -919,17 +986,18 @@ WsLayout wsnet_layout(int B, int M, int training) {
 }
 
 hipError_t wsnet_pack(const float* params, unsigned char* ws, const WsLayout& L, hipStream_t s) {
+  PackArgs a;
+  int most = 0;
   for (int l = 0; l < 4; ++l) {
     const float* w = params + wsnet_param_offset(l);
-    const float* b = w + (size_t)kCout[l] * kCin[l] * 5;
+    a.l[l] = {kCin[l], kCout[l], kCinP[l], kCoutP[l], tpf(l), tpb(l), w,
+              w + (size_t)kCout[l] * kCin[l] * 5, (__bf16*)(ws + L.Wf[l]),
+              (__bf16*)(ws + L.Wb[l]), (float*)(ws + L.bias[l])};
     const int tot = kCoutP[l] * tpf(l) * kCinP[l] + kCinP[l] * tpb(l) * kCoutP[l] + kCoutP[l];
-    hipLaunchKernelGGL(k_pack, dim3((tot + 255) / 256), dim3(256), 0, s, kCin[l], kCout[l],
-                       kCinP[l], kCoutP[l], tpf(l), tpb(l), w, b, (__bf16*)(ws + L.Wf[l]),
-                       (__bf16*)(ws + L.Wb[l]), (float*)(ws + L.bias[l]));
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    most = tot > most ? tot : most;
   }
-  return hipSuccess;
+  hipLaunchKernelGGL(k_pack, dim3((most + 255) / 256, 4), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 // Forward over packed weights: features [B][M][4] FP32 -> out [B][M] FP32.
