@@ -50,67 +50,74 @@ __global__ __launch_bounds__(kBlock) void k_update(int n, int N, int RBX, const 
 
 // The same update for ensembles past the tiled kernels' widths (N > 128 in
 // FP32, 64 in FP64): FP64 products on the 16x16x4 MFMA whatever T is.  A
-// workgroup owns 16 RT whole rows of X_f, kept in LDS in T (so X_a may alias
-// X_f), and its waves take 16-column tiles of W in turn; W comes from L2
-// straight into the MFMA's B operand (16 lanes read 128 consecutive bytes)
-// one step of four ahead.  Lane group lk sums the run lk KQ .. lk KQ + KQ - 1
-// of the summation index.  Bound: FP64 MFMA, 2 n N^2 flops padded to 16
-// (n = 20011, N = 200: one double FMA chain per element took 370 us).
+// workgroup owns 16 RT whole rows, A' in LDS in double (X_f's own term is read
+// again by the lane that writes it, so X_a may alias X_f), and its waves take
+// 16-column tiles of W in turn; W comes from L2 straight into the MFMA's B
+// operand (16 lanes read 128 consecutive bytes).  Lane group lk sums the run lk KQ .. lk KQ + KQ - 1
+// of the summation index.  Bound: FP64 MFMA, 2 n N^2 flops padded to 16, busy a
+// quarter of the time: too few waves cover W's latency and the tail (n = 20011,
+// N = 200: 66 us, one double FMA chain per element 370 us; 13 waves a workgroup
+// 74 us, W four steps ahead 85 us).
+constexpr int kWideBlock = 512;
+
 template <typename T, int RT>
-__global__ __launch_bounds__(kBlock) void k_update_wide(int n, int N, const T* Xf, T* Xa,
-                                                        const double* Wd, int mode,
-                                                        const int* skip) {
-  constexpr int RB = 16 * RT, PAD = 16 / (int)sizeof(T);
+__global__ __launch_bounds__(kWideBlock) void k_update_wide(int n, int N, const T* Xf, T* Xa,
+                                                            const double* Wd, int mode,
+                                                            const int* skip) {
+  constexpr int RB = 16 * RT;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (skip && (*skip & 4)) return;
-  const int TJ = (N + 15) / 16, KQ = 4 * TJ, LD = 16 * TJ + PAD;
-  T* As = (T*)smem_raw;  // RB x LD, zero past n and N
-  __shared__ double mean[RB];
+  const int TJ = (N + 15) / 16, KQ = 4 * TJ, LD = 16 * TJ + 2;
+  double* As = (double*)smem_raw;  // RB x LD: A', zero past n and N
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lk = lane >> 4;
   const int i0 = blockIdx.x * RB, rows = min(RB, n - i0);
-  for (int r = wv; r < RB; r += kBlock / 64)
-    for (int c = lane; c < 16 * TJ; c += 64)
-      As[r * LD + c] = (r < rows && c < N) ? Xf[(size_t)(i0 + r) * N + c] : (T)0;
-  __syncthreads();
-  for (int r = tid / 8; r < RB; r += kBlock / 8) {
-    const int q = tid % 8;
+  for (int r = wv; r < RB; r += kWideBlock / 64) {
     double sum = 0.0;
-    if (mode == 0)
-      for (int c = q; c < N; c += 8) sum += (double)As[r * LD + c];
-    sum = group_sum<8>(sum);
-    if (q == 0) mean[r] = sum / N;
+    for (int c = lane; c < 16 * TJ; c += 64) {
+      const double v = (r < rows && c < N) ? (double)Xf[(size_t)(i0 + r) * N + c] : 0.0;
+      As[r * LD + c] = v;
+      sum += v;
+    }
+    if (mode == 0) {  // (the lane reads back its own elements)
+      const double mu = wave_sum(sum) / N;
+      for (int c = lane; c < N; c += 64) As[r * LD + c] -= mu;
+    }
   }
   __syncthreads();
-  double mu[RT];
-#pragma unroll
-  for (int z = 0; z < RT; ++z) mu[z] = mean[16 * z + lr];
-  for (int tj = wv; tj < TJ; tj += kBlock / 64) {
+  for (int tj = wv; tj < TJ; tj += kWideBlock / 64) {
     const int col = tj * 16 + lr;
     const bool cv = col < N;
     const double* wcol = Wd + (size_t)(lk * KQ) * N + (cv ? col : 0);
     v4d acc[RT];
+    T xo[RT][4];  // the X_f term of mode 0, requested before the products
 #pragma unroll
-    for (int z = 0; z < RT; ++z) acc[z] = v4d{0.0, 0.0, 0.0, 0.0};
-    double bn[4];
-    auto fetch = [&](int t0) {
+    for (int z = 0; z < RT; ++z) {
+      acc[z] = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int r = 16 * z + frag_row<double>(lk, i);
+        xo[z][i] = (mode == 0 && r < rows && cv) ? Xf[(size_t)(i0 + r) * N + col] : (T)0;
+      }
+    }
+    double b1[4], b2[4];  // W of the next step and the one after it
+    auto fetch = [&](int t0, double (&v)[4]) {
 #pragma unroll
       for (int t = 0; t < 4; ++t)
-        bn[t] = (cv && lk * KQ + t0 + t < N) ? wcol[(size_t)(t0 + t) * N] : 0.0;
+        v[t] = (cv && t0 < KQ && lk * KQ + t0 + t < N) ? wcol[(size_t)(t0 + t) * N] : 0.0;
     };
-    fetch(0);
+    fetch(0, b1);
+    fetch(4, b2);
     for (int t0 = 0; t0 < KQ; t0 += 4) {
       double bc[4];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) bc[t] = bn[t];
-      if (t0 + 4 < KQ) fetch(t0 + 4);
+      for (int t = 0; t < 4; ++t) {
+        bc[t] = b1[t];
+        b1[t] = b2[t];
+      }
+      fetch(t0 + 8, b2);
       double av[RT][4];
 #pragma unroll
-      for (int z = 0; z < RT; ++z) {
-        load4d(As + (16 * z + lr) * LD + lk * KQ + t0, av[z]);
-        // columns past N meet zero rows of W; past n the result is dropped
-#pragma unroll
-        for (int t = 0; t < 4; ++t) av[z][t] -= mu[z];
-      }
+      for (int z = 0; z < RT; ++z) load4d(As + (16 * z + lr) * LD + lk * KQ + t0, av[z]);
 #pragma unroll
       for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -121,11 +128,8 @@ __global__ __launch_bounds__(kBlock) void k_update_wide(int n, int N, const T* X
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const int r = 16 * z + frag_row<double>(lk, i);
-        if (r < rows && cv) {
-          double v = acc[z][i];
-          if (mode == 0) v += (double)As[r * LD + col];
-          Xa[(size_t)(i0 + r) * N + col] = (T)v;
-        }
+        if (r < rows && cv)
+          Xa[(size_t)(i0 + r) * N + col] = (T)((double)xo[z][i] + acc[z][i]);
       }
   }
 }
@@ -133,7 +137,7 @@ __global__ __launch_bounds__(kBlock) void k_update_wide(int n, int N, const T* X
 // LDS of a k_update_wide workgroup, and the launch (false: it does not fit).
 template <typename T>
 size_t update_wide_lds(int N, int RT) {
-  return sizeof(T) * (size_t)(16 * RT) * (((N + 15) / 16) * 16 + 16 / sizeof(T));
+  return sizeof(double) * (size_t)(16 * RT) * (((N + 15) / 16) * 16 + 2);
 }
 constexpr size_t kUpdWideLds = 128 * 1024;
 
@@ -144,8 +148,8 @@ hipError_t launch_update_wide(int n, int N, const T* Xf, T* Xa, const double* Wd
   const hipError_t e = hipFuncSetAttribute((const void*)k_update_wide<T, RT>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_update_wide<T, RT>), dim3((n + 16 * RT - 1) / (16 * RT)), dim3(kBlock),
-                     lds, s, n, N, Xf, Xa, Wd, mode, skip);
+  hipLaunchKernelGGL((k_update_wide<T, RT>), dim3((n + 16 * RT - 1) / (16 * RT)),
+                     dim3(kWideBlock), lds, s, n, N, Xf, Xa, Wd, mode, skip);
   return hipGetLastError();
 }
 
@@ -1301,22 +1305,22 @@ __global__ __launch_bounds__(kBlock) void k_red_sum_wide(int N, int NP, int LG, 
   }
 }
 
-// The column CG of k_small_cg for 128 < N <= 256 with G on chip (LG = 64 RPL
-// rows of stride LG, zero outside N x N): eight waves, each with LG/8 rows of
-// G, RR of them in registers and the rest in LDS, since 512 KiB of G at LG =
+// The column CG of k_small_cg for 128 < N <= 256 with G on chip (stride LG = 64
+// RPL, zero outside N x N): eight waves, each with QR rows of G (8 QR >= N), RR
+// of them in registers and the rest in LDS, since 512 KiB of G at LG =
 // 256 fit neither alone.  Every wave carries the whole recurrence and forms
 // its rows' part of q = G p (see k_small_cg_w); the eight parts meet in LDS.
-// Reading G from L2 every step took 378 us for 200 columns.
-template <int RPL>
+// Reading G from L2 every step took 378 us for 200 columns, 16 steps; this 38 us.
+template <int RPL, int QRows>
 struct SmallCgX {
-  static constexpr int LG = 64 * RPL, NW = 8, QR = LG / NW, RR = 24, RL = QR - RR;
+  static constexpr int LG = 64 * RPL, NW = 8, QR = QRows, RR = 24, RL = QR - RR;
   static constexpr size_t lds = sizeof(double) * ((size_t)NW * RL * LG + NW * LG + NW * QR + LG);
 };
-template <int RPL>
+template <int RPL, int QRows>
 __global__ __launch_bounds__(512) void k_small_cg_x(int N, const double* Gp, const double* B,
                                                     double* W, int* iters, int* iters2,
                                                     int* status, double tol, int maxit) {
-  using C = SmallCgX<RPL>;
+  using C = SmallCgX<RPL, QRows>;
   constexpr int LG = C::LG, NW = C::NW, QR = C::QR, RR = C::RR, RL = C::RL;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   double* gl = (double*)smem_raw;         // NW x RL x LG
@@ -1430,14 +1434,14 @@ __global__ __launch_bounds__(512) void k_small_cg_x(int N, const double* Gp, con
   }
 }
 
-template <int RPL>
+template <int RPL, int QR>
 hipError_t launch_small_cg_x(int N, const double* G, const double* B, double* W, int* iters,
                              int* iters2, int* status, double tol, int maxit, hipStream_t s) {
-  constexpr size_t lds = SmallCgX<RPL>::lds;
-  const hipError_t e = hipFuncSetAttribute((const void*)k_small_cg_x<RPL>,
+  constexpr size_t lds = SmallCgX<RPL, QR>::lds;
+  const hipError_t e = hipFuncSetAttribute((const void*)k_small_cg_x<RPL, QR>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_small_cg_x<RPL>, dim3(N), dim3(512), lds, s, N, G, B, W, iters, iters2,
+  hipLaunchKernelGGL((k_small_cg_x<RPL, QR>), dim3(N), dim3(512), lds, s, N, G, B, W, iters, iters2,
                      status, tol, maxit);
   return hipGetLastError();
 }
@@ -1488,7 +1492,7 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
   if constexpr (sizeof(T) == 4)
     if (N <= 128) return launch_update_mfma<T, 128>(n, N, Xf, Xa, Wd, mode, skip, s);
   // larger ensembles: 32 rows a workgroup while they fit its LDS, else 16, else
-  // (N past 2000 in FP32, 1000 in FP64) one double FMA chain per element
+  // (N past 1000) one double FMA chain per element
   if (update_wide_lds<T>(N, 2) <= kUpdWideLds)
     return launch_update_wide<T, 2>(n, N, Xf, Xa, Wd, mode, skip, s);
   if (update_wide_lds<T>(N, 1) <= kUpdWideLds)
@@ -1718,9 +1722,11 @@ hipError_t launch_reduced(int n, int m, int N, int k, const T* Xf, T* Xa, const 
   hipError_t e = red_wide_product<T, false>(ng, m, N, k, Xg, idx, hw, y, rdiag, eps, ws, L, s);
   if (e != hipSuccess) return e;
   if (L.rLG == 192) {
-    e = launch_small_cg_x<3>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s);
-  } else if (L.rLG == 256) {
-    e = launch_small_cg_x<4>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s);
+    e = launch_small_cg_x<3, 24>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s);
+  } else if (L.rLG == 256) {  // eight waves of the fewest rows that hold N
+    e = N <= 208   ? launch_small_cg_x<4, 26>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s)
+        : N <= 224 ? launch_small_cg_x<4, 28>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s)
+                   : launch_small_cg_x<4, 32>(N, G, B, Wd, iters, iters_out, stat, tol, maxit, s);
   } else {  // N > 256: G no longer fits a CU
     hipLaunchKernelGGL(k_small_cg, dim3(N), dim3(kBlock),
                        sizeof(double) * (4 * (size_t)N + kBlock), s, N, (const double*)G,
