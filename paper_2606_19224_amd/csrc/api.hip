@@ -759,7 +759,7 @@ bool batch_layout(int count, const cgd_problem* probs, int prec, BatchLayout* ou
     B.gr.push_back(gr);
     B.ur.push_back(ur);
     B.ngather += (mp + gr - 1) / gr;
-    B.nsolve += probs[b].N;
+    B.nsolve += prec == CGD_FP64 ? probs[b].N : batched_groups(probs[b].N);
     B.nupdate += (probs[b].n + ur - 1) / ur;
     B.sumN += probs[b].N;
   }
@@ -774,11 +774,14 @@ bool batch_layout(int count, const cgd_problem* probs, int prec, BatchLayout* ou
   B.col = take(sizeof(double) * CF_NF * (size_t)B.sumN);
   for (int b = 0; b < count; ++b) {
     const size_t mp = (size_t)B.mp[b], N = (size_t)probs[b].N;
+    // FP32: no z, D lies in r, members in groups of four
+    const bool f64 = prec == CGD_FP64;
+    const size_t cols = f64 ? N : 4 * (size_t)batched_groups(probs[b].N);
     B.Sp.push_back(take(esz * mp * B.NP[b]));
-    B.Dt.push_back(take(esz * mp * N));
-    B.Vz.push_back(take(esz * mp * N));
-    B.Vr.push_back(take(esz * mp * N));
-    B.Vp.push_back(take(esz * mp * N));
+    B.Dt.push_back(f64 ? take(esz * mp * N) : 0);
+    B.Vz.push_back(f64 ? take(esz * mp * N) : 0);
+    B.Vr.push_back(take(esz * mp * cols));
+    B.Vp.push_back(take(esz * mp * cols));
     B.Rp.push_back(take(esz * mp));
     B.Wd.push_back(take(sizeof(double) * N * N));
   }
@@ -822,7 +825,8 @@ cgd_status batch_prepare(int count, const cgd_problem* probs, void* ws, const Ba
     for (int i0 = 0; i0 < B.mp[b]; i0 += B.gr[b]) gtab.push_back(make_int2(b, i0));
     for (int i0 = 0; i0 < q.n; i0 += B.ur[b]) utab.push_back(make_int2(b, i0));
   }
-  // Member solves: workgroup w runs on XCD w % 8, so all members of a problem
+  // Member solves (FP32: four members each): workgroup w runs on XCD w % 8, so all
+  // members of a problem
   // go to one XCD and its S stays in that XCD's L2 while they run.  Problems
   // go, in decreasing order of work, to the XCD with the least work so far;
   // the eight queues are interleaved and padded with empty entries (-1) to
@@ -836,7 +840,8 @@ cgd_status batch_prepare(int count, const cgd_problem* probs, void* ws, const Ba
       int x = 0;
       for (int t = 1; t < kXcd; ++t)
         if (load[t] < load[x]) x = t;
-      for (int j = 0; j < probs[b].N; ++j) q[x].push_back(make_int2(b, j));
+      const int entries = prec == CGD_FP64 ? probs[b].N : batched_groups(probs[b].N);
+      for (int j = 0; j < entries; ++j) q[x].push_back(make_int2(b, j));
       load[x] += (double)B.mp[b] * B.NP[b] * probs[b].N;
     }
     size_t len = 0;

@@ -1289,7 +1289,8 @@ __global__ __launch_bounds__(kCB) void k_cg_columns_wide(CGArgs<T> a, ColArgs<T>
 // ---------------------------------------------------------------------------
 // Batched mode: many independent problems, each solved as above (the same
 // per-member recurrence, stop rule and update), in three launches over work
-// tables, so no workgroup ever waits for another:
+// tables, so no workgroup ever waits for another (FP32 runs the gather and
+// the solve of cg_batched.hip, four members per workgroup):
 //   gather  one entry per (problem, block of P.gr padded rows);
 //   solve   one entry per (problem, member), all members of a problem on one
 //           XCD (entries w with w % 8 equal, padding entries -1), problems in
@@ -1560,6 +1561,11 @@ int batched_shape(int m, int N, int* NP, int* mp, int* RL) {
   const int np = col_np<T>(N);
   if (N < 2 || np == 0) return 0;
   *NP = np;
+  if constexpr (sizeof(T) == 4) {  // cg_batched.hip
+    *mp = batched_rows(m);
+    *RL = 0;
+    return np <= 64 && *mp > 0;
+  }
   if (np == 16) batch_shape_np<T, 16>(m, mp, RL);
   else if (np == 32) batch_shape_np<T, 32>(m, mp, RL);
   else batch_shape_np<T, 64>(m, mp, RL);
@@ -1572,19 +1578,26 @@ hipError_t launch_batched(const BProb<T>* probs, const int2* gtab, int ngather,
                           double tol, int maxit, int precond, int* err, hipEvent_t* ev,
                           hipStream_t s) {
   hipError_t e;
-  hipLaunchKernelGGL(k_bcol_gather<T>, dim3(ngather), dim3(kCB), 0, s, probs, gtab, err,
-                     precond);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  // profiling events bracket the CG launch alone
-  if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
-  const size_t sh = kColLdsMax;
-  if ((e = hipFuncSetAttribute((const void*)k_bcol_solve<T>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh)) != hipSuccess)
-    return e;
-  hipLaunchKernelGGL(k_bcol_solve<T>, dim3(nsolve), dim3(kCB), sh, s, probs, stab, tol, maxit,
-                     err, precond);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
+  if constexpr (sizeof(T) == 4) {
+    if ((e = launch_bm(probs, gtab, ngather, stab, nsolve, tol, maxit, precond, err, ev, s)) !=
+        hipSuccess)
+      return e;
+  } else {
+    hipLaunchKernelGGL(k_bcol_gather<T>, dim3(ngather), dim3(kCB), 0, s, probs, gtab, err,
+                       precond);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // profiling events bracket the CG launch alone
+    if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;
+    const size_t sh = kColLdsMax;
+    if ((e = hipFuncSetAttribute((const void*)k_bcol_solve<T>,
+                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh)) !=
+        hipSuccess)
+      return e;
+    hipLaunchKernelGGL(k_bcol_solve<T>, dim3(nsolve), dim3(kCB), sh, s, probs, stab, tol, maxit,
+                       err, precond);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (ev && (e = hipEventRecord(ev[1], s)) != hipSuccess) return e;
+  }
   const size_t shu = UCfg<T, 64>::lds;
   hipLaunchKernelGGL(k_bcol_update<T>, dim3(nupdate), dim3(kCB), shu, s, probs, utab);
   return hipGetLastError();
