@@ -194,13 +194,11 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, in
                                                                const T* Wtg, int mode,
                                                                const int* skip) {
   using U = UCfg<T, NP>;
-  using V = typename Vec4<T>::type;
-  constexpr int KQ = NP / 4, TJ = NP / 16, VU = 16 / (int)sizeof(T), BS = 64 * kUpdWaves;
-  constexpr int UN = TJ % 2 == 0 ? 2 : 1;  // (an odd count would unroll whole, and spill)
+  constexpr int VU = 16 / (int)sizeof(T), BS = 64 * kUpdWaves;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   if (skip && (*skip & 4)) return;
   T* Wt = (T*)smem_raw;  // NP x LD
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lk = lane >> 4;
+  const int tid = threadIdx.x, wv = tid >> 6;
   if constexpr (WT) {
     constexpr int NC = NP * NP / VU, UL = 8;  // 16-byte chunks, loads in flight per thread
     for (int e0 = tid; e0 < NC; e0 += BS * UL) {
@@ -226,61 +224,9 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, in
   // still spreads over the whole grid
   const int nb = (n + 15) / 16, step = gridDim.x * kUpdWaves;
   for (int b = blockIdx.x + gridDim.x * wv; b < nb; b += step) {
-    const int i0 = b * 16, row = i0 + lr;
-    // A' operand: this lane's columns of row lr, zero past N and past n
-    T av[KQ];
-#pragma unroll
-    for (int c = 0; c < KQ; c += VU) {
-      const int col = 4 * c + VU * lk;
-      if (row < n && col < N) {
-        vload<VU>(Xf + (size_t)row * N + col, *reinterpret_cast<T(*)[VU]>(&av[c]));
-      } else {
-#pragma unroll
-        for (int u = 0; u < VU; ++u) av[c + u] = (T)0;
-      }
-    }
-    if (mode == 0) {
-      double sum = 0.0;
-#pragma unroll
-      for (int t = 0; t < KQ; ++t) sum += (double)av[t];
-      sum += __shfl_xor(sum, 16);
-      sum += __shfl_xor(sum, 32);
-      const double mu = sum / N;
-#pragma unroll
-      for (int t = 0; t < KQ; ++t)
-        av[t] = 4 * (t - t % VU) + VU * lk < N ? (T)((double)av[t] - mu) : (T)0;
-    }
-    // every X_f element of the block's rows is in registers (av) or read below
-    // before this wave stores any of them
-#pragma unroll UN
-    for (int tj = 0; tj < TJ; ++tj) {
-      // X_f at this lane's output elements of the tile (rows frag_row(lk, i),
-      // column lr), requested before the tile's products
-      T xo[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = i0 + frag_row<T>(lk, i), col = tj * 16 + lr;
-        xo[i] = (r < n && col < N) ? Xf[(size_t)r * N + col] : (T)0;
-      }
-      V acc = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};  // two chains
-      const T* wrow = Wt + (tj * 16 + lr) * U::LD + VU * lk;
-#pragma unroll
-      for (int t0 = 0; t0 < KQ; t0 += VU) {
-        T bv[VU];
-        vload<VU>(wrow + 4 * t0, bv);
-#pragma unroll
-        for (int t = 0; t < VU; t += 2) {
-          acc = mfma4(av[t0 + t], bv[t], acc);
-          acc1 = mfma4(av[t0 + t + 1], bv[t + 1], acc1);
-        }
-      }
-      acc += acc1;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int r = i0 + frag_row<T>(lk, i), col = tj * 16 + lr;
-        if (r < n && col < N) Xa[(size_t)r * N + col] = (T)((double)xo[i] + (double)acc[i]);
-      }
-    }
+    T av[NP / 4];
+    update_block_load<T, NP>(n, N, Xf, b, av);
+    update_block_rows<T, NP>(n, N, Xf, Xa, mode, b, av, Wt);
   }
 }
 

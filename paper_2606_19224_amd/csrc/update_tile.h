@@ -290,5 +290,86 @@ __device__ inline void update_tile(int n, int N, const T* Xf, T* Xa, int mode, i
   update_tile_apply<T, NP, BS, RB>(n, N, Xf, Xa, i0, As, Wt);
 }
 
+// One 16-row block of the update by one wave, from registers (its rows loaded
+// apart, so that they can be requested early): lane (lr, lk)
+// holds row lr's columns 4 VU s + VU lk + u, the permutation of the summation
+// index that the B operand (W'^T in LDS, row stride UCfg::LD) uses too, so that
+// a load instruction reads 64 consecutive bytes of each row.  N is a multiple
+// of VU = 16/sizeof(T), Xf and Xa are 16-byte aligned.  Mode 0 centres each row
+// with its mean (the lane's part plus two shuffles across the row's four
+// lanes).  X_f is read again for the output elements before the block's stores,
+// so X_a may alias X_f.
+template <typename T, int NP>
+__device__ __attribute__((always_inline)) inline void update_block_load(int n, int N, const T* Xf,
+                                                                        int b, T (&av)[NP / 4]) {
+  constexpr int KQ = NP / 4, VU = 16 / (int)sizeof(T);
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4, row = b * 16 + lr;
+  // A' operand: this lane's columns of row lr, zero past N and past n
+#pragma unroll
+  for (int c = 0; c < KQ; c += VU) {
+    const int col = 4 * c + VU * lk;
+    if (row < n && col < N) {
+      vload<VU>(Xf + (size_t)row * N + col, *reinterpret_cast<T(*)[VU]>(&av[c]));
+    } else {
+#pragma unroll
+      for (int u = 0; u < VU; ++u) av[c + u] = (T)0;
+    }
+  }
+}
+
+template <typename T, int NP>
+__device__ __attribute__((always_inline)) inline void update_block_rows(
+    int n, int N, const T* Xf, T* Xa, int mode, int b, T (&av)[NP / 4], const T* Wt) {
+  using U = UCfg<T, NP>;
+  using V = typename Vec4<T>::type;
+  constexpr int KQ = NP / 4, TJ = NP / 16, VU = 16 / (int)sizeof(T);
+  constexpr int UN = TJ % 2 == 0 ? 2 : 1;  // (an odd count would unroll whole, and spill)
+  const int lane = threadIdx.x & 63, lr = lane & 15, lk = lane >> 4;
+  const int i0 = b * 16;
+  if (mode == 0) {
+    double sum = 0.0;
+#pragma unroll
+    for (int t = 0; t < KQ; ++t) sum += (double)av[t];
+    sum += __shfl_xor(sum, 16);
+    sum += __shfl_xor(sum, 32);
+    const double mu = sum / N;
+#pragma unroll
+    for (int t = 0; t < KQ; ++t)
+      av[t] = 4 * (t - t % VU) + VU * lk < N ? (T)((double)av[t] - mu) : (T)0;
+  }
+  // every X_f element of the block's rows is in registers (av) or read below
+  // before this wave stores any of them
+#pragma unroll UN
+  for (int tj = 0; tj < TJ; ++tj) {
+    // X_f at this lane's output elements of the tile (rows frag_row(lk, i),
+    // column lr), requested before the tile's products
+    T xo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = i0 + frag_row<T>(lk, i), col = tj * 16 + lr;
+      xo[i] = (r < n && col < N) ? Xf[(size_t)r * N + col] : (T)0;
+    }
+    V acc = {0, 0, 0, 0}, acc1 = {0, 0, 0, 0};  // two chains
+    const T* wrow = Wt + (tj * 16 + lr) * U::LD + VU * lk;
+#pragma unroll
+    for (int t0 = 0; t0 < KQ; t0 += VU) {
+      T bv[VU];
+      vload<VU>(wrow + 4 * t0, bv);
+#pragma unroll
+      for (int t = 0; t < VU; t += 2) {
+        acc = mfma4(av[t0 + t], bv[t], acc);
+        acc1 = mfma4(av[t0 + t + 1], bv[t + 1], acc1);
+      }
+    }
+    acc += acc1;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = i0 + frag_row<T>(lk, i), col = tj * 16 + lr;
+      if (r < n && col < N) Xa[(size_t)r * N + col] = (T)((double)xo[i] + (double)acc[i]);
+    }
+  }
+}
+
 }  // namespace
+
 }  // namespace cgd

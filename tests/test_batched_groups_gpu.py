@@ -13,7 +13,8 @@ from tests.gpu_util import dev_problem, rel, rounded, run, say
 pytestmark = pytest.mark.gpu
 
 SIZES = [(30, 1, 2, 1), (80, 63, 3, 2), (90, 64, 5, 1), (90, 65, 16, 4), (600, 511, 17, 1),
-         (600, 512, 32, 2), (700, 513, 33, 3), (1500, 1089, 47, 1), (4000, 2111, 63, 2),
+         (600, 512, 32, 2), (700, 513, 33, 3), (1217, 400, 44, 2), (300, 90, 20, 1),
+         (1500, 1089, 47, 1), (4000, 2111, 63, 2),
          (4000, 3000, 64, 1)]
 
 
