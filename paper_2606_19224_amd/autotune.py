@@ -156,7 +156,10 @@ def tune_solvers(shapes=SOLVER_SHAPES, precs=("fp32", "fp64"), reps=7, seed=0, l
     for prec in precs:
         for m, N in shapes:
             cls = solver_class(prec, m, N)
-            if cls in seen or cls[1] == 0:
+            # (FP64 past N = 64: the automatic solvers are no candidates, and of those
+            # only the streaming one runs: 14.2 ms at m = 2048, N = 128, where the
+            # automatic choice takes about 1.5 ms at m = 2048, N = 100)
+            if cls in seen or cls[1] == 0 or cls[:2] == ("fp64", 128):
                 continue
             seen.add(cls)
             p = W.random_problem(2 * m, m, N, 1, seed=seed + m + N, tol=1e-6 if prec != "fp64"
