@@ -1056,6 +1056,214 @@ __global__ __launch_bounds__(kCB) void k_cg_columns(CGArgs<T> a, ColArgs<T> ca) 
   column_phase<T, NP, MIX, GV>(a, ca, blockIdx.x, smem_raw);
 }
 
+// Few observation rows (m <= 64 RPL), cold start: the same recurrence by one
+// wave per member, lane = row for q = S g (its rows of S in registers) and lane
+// = column for S^T r (S in LDS), so that a step has no barrier and no partial
+// to add up across waves; the workgroup's other waves wait for the update.  A
+// step is then one wave's serial chain: two short products through LDS
+// broadcasts, the sums' DPP trees, a square root and two divisions.  Lorenz-96, n = 40, m = 20, N =
+// 20, FP64, 16 to 18 steps: whole call 61 us with 8 waves per member, 34 us so.
+constexpr int small_rpl(int NP, size_t esz) { return NP * esz > 256 ? 1 : 2; }
+
+template <typename T, int NP>
+struct SmallCfg {
+  static constexpr int VU = 16 / (int)sizeof(T), LS = NP + VU;
+  static constexpr size_t lds(int rpl) {
+    return sizeof(double) * NP + sizeof(T) * ((size_t)rpl * 64 * LS + NP + rpl * 64);
+  }
+};
+
+// LDS traffic between the lanes of one wave: in order in hardware, so only
+// the compiler has to keep it in order.
+__device__ inline void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <typename T, int NP, int RPL>
+__global__ __launch_bounds__(kCB) void k_cg_columns_small(CGArgs<T> a, ColArgs<T> ca) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  using K = KC<T, NP, false>;
+  using C = SmallCfg<T, NP>;
+  constexpr int MR = 64 * RPL, VU = C::VU, LS = C::LS;
+  constexpr int CH = NP >= 64 ? 8 : 4;   // chains of a row's product
+  constexpr int CK = 8;                  // rows of a column's sum held in T
+  const int tid = threadIdx.x, lane = tid & 63, j = blockIdx.x;
+  const int N = a.N, m = a.m, mp = ca.mp;
+  const double inv = 1.0 / (double)(N - 1);
+  const T invT = (T)inv;
+  double* Wc = (double*)smem_raw;
+  T* Ss = (T*)(Wc + NP);                 // MR x LS
+  T* gT = Ss + (size_t)MR * LS;          // NP: G as the rows use it
+  T* rT = gT + NP;                       // MR: r as the columns use it
+  fold_gather_errors(a);
+  unsigned long long census_count = 0;
+  if (a.census && tid == 0) census_count = census_arrive(a.census);
+  T sr[RPL][NP], r[RPL], p[RPL], z[RPL], d[RPL], rv[RPL];
+  if (tid < 64) {
+#pragma unroll
+    for (int h = 0; h < RPL; ++h) {
+      const int i = lane + 64 * h;
+#pragma unroll
+      for (int c = 0; c < NP; c += VU) {
+        const int cl = c / K::C, v = (c % K::C) / VU;
+        vload<VU>(ca.Sp + (((size_t)v * mp + i) * K::L + cl) * VU,
+                  *reinterpret_cast<T(*)[VU]>(&sr[h][c]));
+      }
+      d[h] = ca.Dt[(size_t)j * mp + i];
+      rv[h] = i < m ? effective_r(a, i) : (T)0;
+      r[h] = d[h];
+      p[h] = 0;
+      z[h] = 0;
+    }
+  }
+  // every workgroup must be resident before any wait on another one
+  if (a.census && !census_wait(a.census, a.err, a.census_ticks, census_count)) return;
+  if (tid < 64) {
+#pragma unroll
+    for (int h = 0; h < RPL; ++h)
+#pragma unroll
+      for (int c = 0; c < NP; ++c) Ss[(size_t)(lane + 64 * h) * LS + c] = sr[h][c];
+    const int col = lane % NP;  // (lanes past NP repeat a column and are not used)
+    // column sums of S^T r in double over chunks of CK rows in T
+    auto gram = [&]() {
+#pragma unroll
+      for (int h = 0; h < RPL; ++h) rT[lane + 64 * h] = r[h];
+      wave_lds_fence();
+      double sum = 0.0;
+#pragma unroll 2
+      for (int i = 0; i < m; i += CK) {
+        T x[CK], acc = 0, acc1 = 0;
+        vload<CK>(rT + i, x);
+#pragma unroll
+        for (int u = 0; u < CK; u += 2) {
+          acc += Ss[(size_t)(i + u) * LS + col] * x[u];
+          acc1 += Ss[(size_t)(i + u + 1) * LS + col] * x[u + 1];
+        }
+        sum += (double)(acc + acc1);
+      }
+      return sum;
+    };
+    auto dots = [&](T (&q)[RPL]) {
+      T g[RPL][CH];
+#pragma unroll
+      for (int h = 0; h < RPL; ++h)
+#pragma unroll
+        for (int u = 0; u < CH; ++u) g[h][u] = 0;
+#pragma unroll
+      for (int c = 0; c < NP; c += VU) {
+        T gv[VU];
+        vload<VU>(gT + c, gv);
+#pragma unroll
+        for (int u = 0; u < VU; ++u)
+#pragma unroll
+          for (int h = 0; h < RPL; ++h) g[h][(c + u) % CH] += sr[h][c + u] * gv[u];
+      }
+#pragma unroll
+      for (int h = 0; h < RPL; ++h) {
+        T t = (g[h][0] + g[h][1]) + (g[h][2] + g[h][3]);
+        if constexpr (CH == 8) t += (g[h][4 % CH] + g[h][5 % CH]) + (g[h][6 % CH] + g[h][7 % CH]);
+        q[h] = t;
+      }
+    };
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;
+#pragma unroll
+    for (int h = 0; h < RPL; ++h) {
+      s0 += (double)(r[h] * r[h]);
+      s1 += (double)(rv[h] * r[h] * r[h]);
+    }
+    s0 = wave_sum(s0);
+    s1 = wave_sum(s1);
+    const double dn = s0, thr = a.tol * sqrt(dn);
+    double gr = gram(), gc = 0.0, wc = 0.0, rhoprev = 0.0;
+    int status = COL_RUNNING, iters = 0;
+    for (int kit = 0;; ++kit) {
+      const double rho = s0;
+      iters = kit;
+      if (sqrt(rho) <= thr) {
+        status = COL_CONVERGED;
+        break;
+      }
+      if (kit >= a.maxit) {
+        status = COL_MAXIT;
+        break;
+      }
+      const double beta = kit == 0 ? 0.0 : rho / rhoprev;
+      // new G = S^T p, rounded as the products use it, and its squared norm
+      const double gk = (double)(T)(gr + beta * gc);
+      if (lane < NP) gT[lane] = (T)gk;
+      const double gg = wave_sum(lane < NP ? gk * gk : 0.0);
+      const double alpha = rho / (gg * inv + s1 + 2.0 * beta * s2 + beta * beta * s3);
+      if (!isfinite(alpha) || !isfinite(beta)) {
+        status = COL_NONFINITE;
+        break;
+      }
+      gc = gk;
+      wc += alpha * gk;
+      rhoprev = rho;
+      wave_lds_fence();
+      T q[RPL];
+      dots(q);
+      const T al = (T)alpha, be = (T)beta;
+      s0 = s1 = s2 = s3 = 0.0;
+#pragma unroll
+      for (int h = 0; h < RPL; ++h) {
+        p[h] = r[h] + be * p[h];
+        const T qq = q[h] * invT + rv[h] * p[h];
+        z[h] += al * p[h];
+        r[h] -= al * qq;
+        const T rr = rv[h] * r[h];
+        s0 += (double)(r[h] * r[h]);
+        s1 += (double)(rr * r[h]);
+        s2 += (double)(rr * p[h]);
+        s3 += (double)(rv[h] * p[h] * p[h]);
+      }
+      gr = gram();
+      s0 = wave_sum(s0);
+      s1 = wave_sum(s1);
+      s2 = wave_sum(s2);
+      s3 = wave_sum(s3);
+    }
+    // the column's results (as column_phase leaves them)
+    if (lane == 0) {
+      a.coli[CI_ITERS * N + j] = iters;
+      a.coli[CI_STATUS * N + j] = status;
+      a.coli[CI_FALLBACK * N + j] = 0;
+      a.col[CF_DN * N + j] = dn;
+      if (a.iters_out) a.iters_out[j] = iters;
+    }
+    if (lane < NP) Wc[lane] = wc;
+    if (lane < N) a.Wd[(size_t)lane * N + j] = wc * inv;
+    if (a.z_out)
+#pragma unroll
+      for (int h = 0; h < RPL; ++h)
+        if (lane + 64 * h < m) a.z_out[(size_t)(lane + 64 * h) * N + j] = z[h];
+    if (a.want_relres) {
+      wave_lds_fence();
+      double res2 = 0.0;
+#pragma unroll
+      for (int h = 0; h < RPL; ++h) {
+        double dp[2] = {0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < NP; ++c) dp[c & 1] += (double)sr[h][c] * (double)(T)(Wc[c] * inv);
+        const double res = (double)d[h] - (dp[0] + dp[1]) - (double)rv[h] * (double)z[h];
+        res2 += res * res;
+      }
+      res2 = wave_sum(res2);
+      if (lane == 0) {
+        const double rr2 = dn > 0 ? sqrt(res2 / dn) : 0.0;
+        a.relres[j] = rr2;
+        if (a.relres_out) a.relres_out[j] = rr2;
+      }
+    }
+  }
+  __syncthreads();
+  split_publish_w<T>(N, j, Wc, inv, ca.wb);
+  __syncthreads();
+  split_update_rows<T, NP>(a, ca.wb, smem_raw);
+}
+
 // The gather of S, D (and diag(R)) as a launch of its own, one row step per
 // workgroup, ahead of the solvers that then read them with no grid-wide wait.
 // With a.gerr set, workgroups past the ng gather ones clear the solver's
@@ -1167,6 +1375,13 @@ hipError_t launch_np(const CGArgs<T>& a, const ColArgs<T>& vec, hipEvent_t* ev, 
   if (ev && (e = hipEventRecord(ev[0], s)) != hipSuccess) return e;  // the solver launch alone
   const size_t sh = col_lds<T, NP, MIX, GV>(ca.mp, ca.RL);
   auto fn = k_cg_columns<T, NP, MIX, GV>;
+  if constexpr (!MIX && !GV && NP <= 64) {
+    // few rows (two per lane where their S fits the registers), cold start and
+    // no phase trace: one wave per member
+    constexpr int RPL = small_rpl(NP, sizeof(T));
+    if (!a.z0 && !a.trace && a.m <= 64 * RPL && SmallCfg<T, NP>::lds(RPL) <= sh)
+      fn = a.m <= 64 ? k_cg_columns_small<T, NP, 1> : k_cg_columns_small<T, NP, RPL>;
+  }
   e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)sh);
   if (e != hipSuccess) return e;
   // the workgroups wait for each other's published W before the update:
