@@ -25,9 +25,12 @@
 // Bound: the MFMA, LDS and L2 paths of a tile are within a factor of two of
 // each other.  One workgroup per member on the vector ALUs re-read S from L2
 // for every member and was bound by that: 64 filters of 1024 to 32768
-// variables took 961 us in the solve; four members per workgroup take 634 us
+// variables took 961 us in the solve; four members per workgroup take 615 us
 // (and 111 -> 67 us for the gather, which no longer writes a second layout).
-// 12 waves with half tiles each spilled (942 us).
+// 12 waves with half tiles each spilled (942 us).  The sums by halving exchanges
+// and the first tile's S requested before the decisions matter where a wave has
+// one tile: 8 filters of up to 2048 variables, whole call 131 us without and 106
+// us with both (124 us one workgroup per member).
 #include <type_traits>
 #include <utility>
 
@@ -76,15 +79,68 @@ __device__ inline float quad(float v) {
   return dpp<I * 0x55>(v);
 }
 
-// One pass over the problem's rows.  STEP: p = r + beta p, q = S g/(N-1) + R
+// Sum of v[lane % 16] over the wave, in double, from every lane's 16 values: each
+// exchange halves the values a lane keeps (15 exchanges and two more across the
+// rows of 16 lanes, where a tree per value takes six each).
+__device__ __attribute__((always_inline)) inline double wave_sums16(const double (&v)[16],
+                                                                    int lane) {
+  double a[8], b[4], c[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const bool hi = lane & 8;
+    a[i] = (hi ? v[8 + i] : v[i]) + dpp<0x140>(hi ? v[i] : v[8 + i]);  // row_mirror
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bool hi = lane & 4;
+    b[i] = (hi ? a[4 + i] : a[i]) + dpp<0x141>(hi ? a[i] : a[4 + i]);  // row_half_mirror
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const bool hi = lane & 2;
+    c[i] = (hi ? b[2 + i] : b[i]) + dpp<0x4E>(hi ? b[i] : b[2 + i]);   // lane ^ 2
+  }
+  const bool hi = lane & 1;
+  double d = (hi ? c[1] : c[0]) + dpp<0xB1>(hi ? c[0] : c[1]);         // lane ^ 1
+  d += __shfl_xor(d, 16);
+  return d + __shfl_xor(d, 32);
+}
+
+// A wave's rows of a tile.  S of its first tile is requested at the end of the
+// pass before, so that the decisions between two passes cover the latency (r
+// and p as well would spill).
+template <int NP>
+struct BmTile {
+  v4f s[BM<NP>::NQ], r, p;
+  float w;
+};
+template <int NP>
+__device__ __attribute__((always_inline)) inline void bm_load_s(int mp, const float* S, int t,
+                                                                BmTile<NP>& x) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int q = 0; q < BM<NP>::NQ; ++q)
+    x.s[q] = *reinterpret_cast<const v4f*>(S + ((size_t)q * mp + t * kTR + lane) * 4);
+}
+template <int NP>
+__device__ __attribute__((always_inline)) inline void bm_load_v(bool step, const float* R4,
+                                                                const float* P4, const float* rv,
+                                                                int t, BmTile<NP>& x) {
+  const int i = t * kTR + (threadIdx.x & 63);
+  x.r = *reinterpret_cast<const v4f*>(R4 + (size_t)i * 4);
+  if (step) x.p = *reinterpret_cast<const v4f*>(P4 + (size_t)i * 4);
+  x.w = rv[i];
+}
+
+// One pass over the problem's rows, S of the first tile in x.  STEP: p = r + beta p, q = S g/(N-1) + R
 // p, r -= alpha q first (gr: this lane's g, entry e of lane 4 q + m is g[4 q
 // + e] of member m); else r = d as it lies in memory.  Leaves this wave's part
 // of S^T r in its tile ([lane][member], lane % NP the column) and its sums
 // (r.r, r.Rr, r.Rp, p.Rp per member) in sh.wsum.
 template <int NP, bool STEP>
-__device__ __attribute__((always_inline)) inline void bm_pass(int mp, const float* S, float* R4, float* P4,
-                                      const float* rv, float inv, const float (&gr)[4],
-                                      const BShared& shc, BShared& sh, float* tile) {
+__device__ __attribute__((always_inline)) inline void bm_pass(
+    int mp, const float* S, float* R4, float* P4, const float* rv, float inv, const float (&gr)[4],
+    BShared& sh, float* tile, BmTile<NP>& x) {
   using C = BM<NP>;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nt = mp / kTR;
   const int n = lane & 3;
@@ -92,9 +148,9 @@ __device__ __attribute__((always_inline)) inline void bm_pass(int mp, const floa
   bool on[4];
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
-    al[m] = STEP ? shc.al[m] : 0.f;
-    be[m] = STEP ? shc.be[m] : 0.f;
-    on[m] = STEP && shc.mode[m] == MODE_STEP;
+    al[m] = STEP ? sh.al[m] : 0.f;
+    be[m] = STEP ? sh.be[m] : 0.f;
+    on[m] = STEP && sh.mode[m] == MODE_STEP;
   }
   double gd[4] = {0.0, 0.0, 0.0, 0.0};
   float sm[4][4];  // (a lane adds one row per tile; lanes and waves in double)
@@ -102,27 +158,12 @@ __device__ __attribute__((always_inline)) inline void bm_pass(int mp, const floa
   for (int m = 0; m < 4; ++m)
 #pragma unroll
     for (int f = 0; f < 4; ++f) sm[m][f] = 0.f;
-  v4f s[C::NQ], r, p = v4f{0, 0, 0, 0};
-  float w = 0.f;
-  auto load_s = [&](int t) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < C::NQ; ++q)
-      s[q] = *reinterpret_cast<const v4f*>(S + ((size_t)q * mp + t * kTR + lane) * 4);
-  };
-  auto load_v = [&](int t) __attribute__((always_inline)) {
-    r = *reinterpret_cast<const v4f*>(R4 + (size_t)(t * kTR + lane) * 4);
-    if (STEP) p = *reinterpret_cast<const v4f*>(P4 + (size_t)(t * kTR + lane) * 4);
-    w = rv[t * kTR + lane];
-  };
   int t = wv;
-  if (t < nt) {
-    load_s(t);
-    load_v(t);
-  }
+  if (t < nt) bm_load_v<NP>(STEP, R4, P4, rv, t, x);
   for (; t < nt; t += kBW) {
     // S rows to the LDS tile, and the first product from the registers
 #pragma unroll
-    for (int q = 0; q < C::NQ; ++q) *reinterpret_cast<v4f*>(tile + lane * C::LDT + 4 * q) = s[q];
+    for (int q = 0; q < C::NQ; ++q) *reinterpret_cast<v4f*>(tile + lane * C::LDT + 4 * q) = x.s[q];
     v4f qa[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) qa[e] = v4f{0, 0, 0, 0};
@@ -130,23 +171,23 @@ __device__ __attribute__((always_inline)) inline void bm_pass(int mp, const floa
       each(std::make_integer_sequence<int, C::NQ>{}, [&](auto qc) __attribute__((always_inline)) {
         constexpr int q = decltype(qc)::value;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) qa[e] = mfma_b<4, q>(gr[e], s[q][e], qa[e]);
+        for (int e = 0; e < 4; ++e) qa[e] = mfma_b<4, q>(gr[e], x.s[q][e], qa[e]);
       });
-    if (t + kBW < nt) load_s(t + kBW);
-    v4f rn = r, pn = p;
-    const float wr = w;
+    if (t + kBW < nt) bm_load_s<NP>(mp, S, t + kBW, x);
+    v4f rn = x.r, pn = v4f{0, 0, 0, 0};
+    const float wr = x.w;
     if constexpr (STEP) {
       const v4f qs = (qa[0] + qa[1]) + (qa[2] + qa[3]);
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        pn[m] = be[m] != 0.f ? r[m] + be[m] * p[m] : r[m];  // (p is not set before the first step)
+        pn[m] = be[m] != 0.f ? x.r[m] + be[m] * x.p[m] : x.r[m];  // (p is not set before the first step)
         const float q = qs[m] * inv + wr * pn[m];
-        rn[m] = on[m] ? r[m] - al[m] * q : r[m];
+        rn[m] = on[m] ? x.r[m] - al[m] * q : x.r[m];
       }
       *reinterpret_cast<v4f*>(R4 + (size_t)(t * kTR + lane) * 4) = rn;
       *reinterpret_cast<v4f*>(P4 + (size_t)(t * kTR + lane) * 4) = pn;
     }
-    if (t + kBW < nt) load_v(t + kBW);
+    if (t + kBW < nt) bm_load_v<NP>(STEP, R4, P4, rv, t + kBW, x);
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
       const float rr = wr * rn[m];
@@ -189,13 +230,17 @@ __device__ __attribute__((always_inline)) inline void bm_pass(int mp, const floa
   double* red = reinterpret_cast<double*>(tile);
 #pragma unroll
   for (int m = 0; m < 4; ++m) red[lane * 4 + m] = gd[m];
+  double v[16];
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
-    for (int f = 0; f < 4; ++f) {
-      const double v = wave_sum((double)sm[m][f]);
-      if (lane == 0) sh.wsum[wv][4 * m + f] = v;
-    }
+    for (int f = 0; f < 4; ++f) v[4 * m + f] = (double)sm[m][f];
+  const double sum = wave_sums16(v, lane);
+  if (lane < 16) sh.wsum[wv][lane] = sum;
+  __builtin_amdgcn_sched_barrier(0);  // (earlier, the tile's registers would spill)
+  if (wv < nt) {
+    bm_load_s<NP>(mp, S, wv, x);
+  }
 }
 
 // Four members 4 g .. of one problem.
@@ -215,7 +260,9 @@ __device__ __attribute__((always_inline)) inline void bm_solve(const BProb<float
   bool active = true, fresh = true;
   int iters = 0, status = COL_RUNNING;
   float gr[4] = {0.f, 0.f, 0.f, 0.f};
-  bm_pass<NP, false>(P.mp, P.Sp, R4, P4, P.Rp, (float)inv, gr, sh, sh, tile);
+  BmTile<NP> x;
+  if (wv < P.mp / kTR) bm_load_s<NP>(P.mp, P.Sp, wv, x);
+  bm_pass<NP, false>(P.mp, P.Sp, R4, P4, P.Rp, (float)inv, gr, sh, tile, x);
   for (int kit = 0;; ++kit) {
     __syncthreads();
     double rho = 0.0, sa = 0.0, sb = 0.0, sc = 0.0, gk = 0.0, beta = 0.0;
@@ -289,7 +336,7 @@ __device__ __attribute__((always_inline)) inline void bm_solve(const BProb<float
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       gr[e] = lane < NP ? sh.g4[((lane & ~3) + e) * 4 + (lane & 3)] : 0.f;
-    bm_pass<NP, true>(P.mp, P.Sp, R4, P4, P.Rp, (float)inv, gr, sh, sh, tile);
+    bm_pass<NP, true>(P.mp, P.Sp, R4, P4, P.Rp, (float)inv, gr, sh, tile, x);
   }
   if (!dec || j >= N) return;
   if (k < N) P.Wd[(size_t)k * N + j] = Wc * inv;
