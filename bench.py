@@ -79,11 +79,6 @@ MEASURED_TRAFFIC = {
         "fetch_kib_raw": 619065.8, "fetch_scale": 2.0, "write_kib_raw": 1243155.9,
         "write_scale": 1.0,
     },
-    "k_bcol_solve": {
-        "sources": _COL_SOURCES, "sha256_16": "1736167553f42ff5",
-        "fetch_kib_raw": 346812.2, "fetch_scale": 2.0, "write_kib_raw": 2171608.0,
-        "write_scale": 1.0,
-    },
     "k_kt_cg": {
         "workload": "l96-twin", "sources": _KT_SOURCES, "sha256_16": "ae42694e5d9a805d",
         "fetch_kib_raw": 859089.8, "fetch_scale": 2.0, "write_kib_raw": 1706403.9,
@@ -772,13 +767,13 @@ def bench_batched(args):
                      "min_of_max": int(it_max.min())},
         "roofline": {
             "bound": "hbm",
-            "kernel": "k_bcol_solve<float> (one workgroup per member of every filter); the "
-                      "step also runs k_bcol_gather and k_bcol_update",
+            "kernel": "k_bm_solve (one workgroup per four members of every filter); the "
+                      "step also runs k_bm_gather and k_bcol_update",
             "achieved": round(achieved, 2),
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 5),
-            "traffic": measured_traffic("k_bcol_solve"),
+            "traffic": measured_traffic("k_bm_solve"),
             "avg_launch_us": round(solve_ms.mean() * 1e3, 2),
             "alg_bytes_per_launch": float(bytes_alg),
             "graph_replay_avg_us": round(per_ms.mean() * 1e3, 2),

@@ -332,8 +332,8 @@ cgd_status cgd_enkf_gain_analysis(int n, int m, int N, int k,
  * per-member solver (same recurrence, stop rule and update).  One call is
  * three launches over work tables: the gather of S and D (one workgroup per
  * gather_rows padded observation rows of a problem), the CG (one workgroup
- * per member of a problem, all members of a problem on one XCD so its S stays
- * in that L2, problems in decreasing order of work, the vectors in the
+ * per four members of a problem in FP32, per member in FP64, all members of a
+ * problem on one XCD so its S stays in that L2, problems in decreasing order of work, the vectors in the
  * workspace so any m fits), and the ensemble update (one workgroup per
  * update_rows state rows).  No workgroup waits for another.  The row counts
  * are per problem (see cgd_problem); invalid ones make the workspace size 0
@@ -412,6 +412,7 @@ cgd_status cgd_tridiag_cholesky(int m, const void* r_diag, const void* r_offdiag
  *   solver:          1 = streaming cooperative solver, 2 = resident solver,
  *                    3 = per-member column solver, 4 = split per-member solver,
  *                    5 = row-block x member-group solver
+ *                    (3 and 5 also in FP64 for 64 < N <= 128, automatic only)
  *   rows_per_block:  observation rows per workgroup block (kinds 1, 2, 4, 5)
  *   workgroups:      workgroups of the solver launch
  * Returns CGD_OK, CGD_ERR_ARG for invalid sizes/options or NULL outputs,

@@ -1087,7 +1087,7 @@ __global__ __launch_bounds__(kBlock) void k_red_update(int n, int N, const T* Xf
 // ---------------------------------------------------------------------------
 
 // Row i of Q, one wave per row.  HX is kept in the row's left half until its
-// mean is known.  errw and SEN as in k_red_prep.
+// mean is known.  errw: an error word per workgroup; SEN: the sEnKF's row scale.
 template <typename T, bool SEN>
 __global__ __launch_bounds__(kBlock) void k_red_prep_wide(int n, int m, int N, int NP, int k,
                                                           const T* Xf, const int32_t* idx,
@@ -1145,7 +1145,7 @@ __global__ __launch_bounds__(kBlock) void k_red_prep_wide(int n, int m, int N, i
 }
 
 // part[s] = Q[rows of chunk s, :NP]^T Q[rows of chunk s, :], tiles t0 .. of
-// the tile list of k_red_gemm.  All tiles of a chunk run on one XCD
+// the tile list (all of the right half, the left half's lower tiles skipped).  All tiles of a chunk run on one XCD
 // (workgroup w runs on XCD w mod 8), whose L2 then serves the chunk's rows to
 // every tile after the first.
 __global__ __launch_bounds__(kBlock) void k_red_gemm_wide(int NP, int KC, int mpad, int S, int t0,
