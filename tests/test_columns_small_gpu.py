@@ -52,3 +52,36 @@ def test_parity(lib, n, m, N, k, prec):
     inplace = lib.analysis(**a, tol=tol, maxit=p.maxit, prec=prec, out=a["Xf"], stats=False)
     torch.cuda.synchronize()
     assert torch.equal(first, inplace["Xa"])   # repeatable, and X_a may alias X_f
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+def test_launch_modes_capture_and_bad_index(lib, prec):
+    import torch
+    bar = 1e-10 if prec == "fp64" else 1e-4
+    tol = 1e-12 if prec == "fp64" else 1e-6
+    p = W.random_problem(60, 30, 20, 2, seed=5, tol=tol)
+    q = W.random_problem(60, 30, 20, 2, seed=6, tol=tol)
+    want = [O.enkf_analysis(x.Xf, x.idx, x.w, x.y, x.r, x.eps)["Xa"] for x in (p, q)]
+    assert rel(run(lib, p, prec, cooperative=True)["Xa"], want[0]) <= bar
+    assert rel(run(lib, p, prec, solver=3)["Xa"], want[0]) <= bar
+    # captured once, replayed on changed inputs with eager work in between
+    a, b = dev_problem(p, prec), dev_problem(q, prec)
+    plan = lib.Plan(60, 30, 20, 2, prec=prec, tol=tol, maxit=1000)
+    out = torch.empty_like(a["Xf"])
+    plan(a["Xf"], a["idx"], a["w"], a["y"], a["r"], a["eps"], out)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        plan(a["Xf"], a["idx"], a["w"], a["y"], a["r"], a["eps"], out)
+    first = {k: v.clone() for k, v in a.items() if v is not None}
+    for which in (0, 1, 0, 1):
+        for k, v in (first, b)[which].items():
+            if v is not None:
+                a[k].copy_(v)
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert rel(out.double().cpu().numpy(), want[which]) <= bar
+    p.idx[7, 0] = 60
+    assert run(lib, p, prec, raise_on_error=False)["status"] == -2
