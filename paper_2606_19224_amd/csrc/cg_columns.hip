@@ -1062,7 +1062,8 @@ __global__ __launch_bounds__(kCB) void k_cg_columns(CGArgs<T> a, ColArgs<T> ca) 
 // to add up across waves; the workgroup's other waves wait for the update.  A
 // step is then one wave's serial chain: two short products through LDS
 // broadcasts, the sums' DPP trees, a square root and two divisions.  Lorenz-96, n = 40, m = 20, N =
-// 20, FP64, 16 to 18 steps: whole call 61 us with 8 waves per member, 34 us so.
+// 20, FP64, 16 to 18 steps: whole call 61 us with 8 waves per member, 29 us so (34 us
+// with 8 rows of S^T r at a time); m = 128, N = 32, FP32: 2.7 -> 1.4 us a step.
 constexpr int small_rpl(int NP, size_t esz) { return NP * esz > 256 ? 1 : 2; }
 
 template <typename T, int NP>
@@ -1089,6 +1090,8 @@ __global__ __launch_bounds__(kCB) void k_cg_columns_small(CGArgs<T> a, ColArgs<T
   constexpr int MR = 64 * RPL, VU = C::VU, LS = C::LS;
   constexpr int CH = NP >= 64 ? 8 : 4;   // chains of a row's product
   constexpr int CK = 8;                  // rows of a column's sum held in T
+  // rows of S^T r with their LDS reads in flight (32 would spill beside 64 doubles a lane)
+  constexpr int GR = sizeof(T) * NP * RPL >= 512 && sizeof(T) == 8 ? 16 : 32;
   const int tid = threadIdx.x, lane = tid & 63, j = blockIdx.x;
   const int N = a.N, m = a.m, mp = ca.mp;
   const double inv = 1.0 / (double)(N - 1);
@@ -1131,17 +1134,24 @@ __global__ __launch_bounds__(kCB) void k_cg_columns_small(CGArgs<T> a, ColArgs<T
 #pragma unroll
       for (int h = 0; h < RPL; ++h) rT[lane + 64 * h] = r[h];
       wave_lds_fence();
+      // GR rows at a time, their LDS reads in flight together (rows past m are 0)
       double sum = 0.0;
-#pragma unroll 2
-      for (int i = 0; i < m; i += CK) {
-        T x[CK], acc = 0, acc1 = 0;
-        vload<CK>(rT + i, x);
+#pragma unroll 1
+      for (int i0 = 0; i0 < m; i0 += GR) {
+        T x[GR], y[GR];
+        vload<GR>(rT + i0, x);
 #pragma unroll
-        for (int u = 0; u < CK; u += 2) {
-          acc += Ss[(size_t)(i + u) * LS + col] * x[u];
-          acc1 += Ss[(size_t)(i + u + 1) * LS + col] * x[u + 1];
+        for (int u = 0; u < GR; ++u) y[u] = Ss[(size_t)(i0 + u) * LS + col];
+#pragma unroll
+        for (int c = 0; c < GR; c += CK) {
+          T acc = 0, acc1 = 0;
+#pragma unroll
+          for (int u = 0; u < CK; u += 2) {
+            acc += y[c + u] * x[c + u];
+            acc1 += y[c + u + 1] * x[c + u + 1];
+          }
+          sum += (double)(acc + acc1);
         }
-        sum += (double)(acc + acc1);
       }
       return sum;
     };
