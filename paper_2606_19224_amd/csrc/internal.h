@@ -281,9 +281,9 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
                          hipStream_t s, const int* skip = nullptr);
 // Geometry of the reduced mode for N <= 128: N padded to NP (32, 64 or 128), m
 // padded to mpad (a multiple of 32), KC rows per chunk of the N x 2N product
-// and S parts of it.  0 when N is out of range.
-int reduced_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
-size_t reduced_part_elems(int m, int N);  // elements of one chunk's (or workgroup's) part
+// and S parts of it (esz: bytes per value).  0 when N is out of range.
+int reduced_shape(int m, int N, int esz, int* NP, int* mpad, int* KC, int* S);
+size_t reduced_part_bytes(int m, int N, int esz);  // one chunk's (or workgroup's) part
 // The same for N > 128: NP a multiple of 64, mpad, KC and S as above.
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
 // Xg (ng rows) is the array the observations are gathered from; Xf is

@@ -548,12 +548,14 @@ __global__ __launch_bounds__(kBlock) void k_red_pg(int n, int m, int N, int k, c
 // s + gridDim.x, .. of 32 observation rows: it builds a chunk of Q in one of
 // two LDS buffers, stored by column as in k_red_pg, and multiplies it there;
 // each wave keeps its share of the output's 16 x 16 tiles (the upper tiles of
-// the symmetric left half, every tile of the right half) in accumulators until
-// the last chunk.  A chunk's indices are requested two chunks ahead and its
-// rows one chunk ahead, under the previous chunk's products.  Thread q of a
-// row takes the members q, q + 32, .. (coalesced reads; its LDS stores fall on
-// distinct banks).  part[s][tile][16][16]; errw and SEN (right half only) as in
-// k_red_pg.
+// the symmetric left half, every tile of the right half) until the last chunk.  FP32
+// chains don't grow with m: up to N = 64 a chunk's product is added to its tile's sum
+// in double, past that (where those sums would spill) a workgroup takes at most
+// kRsChain chunks.  A chunk's indices are requested two chunks ahead and its rows one
+// chunk ahead, under the previous chunk's
+// products.  Thread q of a row takes the members q, q + 32, .. (coalesced reads; its
+// LDS stores fall on distinct banks).  part[s][tile][16][16] in RsPart; errw and
+// SEN (right half only) as in k_red_pg.
 // Bound: the MFMA in FP64, the gather's latency in FP32.  At m = 10^5, N =
 // 100 in FP64 the two launches this replaces, with 205 MB of Q between them,
 // took 119 + 171 us, this one 119 us; at m = 16384, N = 128, k = 4 in FP32 (the
@@ -576,6 +578,20 @@ struct RsCfg {
   static constexpr int NT = NTL + TN * TN;
   static constexpr int TPW = (NT + kRsWaves - 1) / kRsWaves;  // tiles per wave
 };
+// FP32, N <= 64: sums and parts in double, as these sizes added one FP32 part per 32
+// rows in double before they were streamed (m = 10^5, N = 48, relative error of P^T P
+// against 64-bit sums: 2.3e-9 so, 2.1e-8 with FP32 chains over a workgroup's rows).
+// Past that 512 rows at most (the launches before took a 73rd of m).
+template <typename T, int TN>
+using RsPart = std::conditional_t<TN <= 4, double, T>;
+constexpr int kRsChain = 16;
+// Workgroups at m, N: one a CU where that keeps the chains short.
+inline int red_stream_groups(int m, int N, int esz) {
+  const int nch = (m + kRsRows - 1) / kRsRows;
+  int g = kRsGroups;
+  if (esz == 4 && N > 64 && nch > kRsChain * g) g = (nch + kRsChain - 1) / kRsChain;
+  return nch < g ? nch : g;
+}
 template <typename T, int TN>
 constexpr size_t red_stream_lds() {
   return sizeof(T) * 2 * (size_t)(32 * TN) * (kRsRows + 16 / sizeof(T));
@@ -585,9 +601,11 @@ template <typename T, int TN, bool SEN>
 __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, int k, int nch,
                                                            const T* Xf, const int32_t* idx,
                                                            const T* hw, const T* y,
-                                                           const T* rdiag, const T* eps, T* part,
-                                                           int* errw) {
+                                                           const T* rdiag, const T* eps,
+                                                           RsPart<T, TN>* part, int* errw) {
   using C = RsCfg<TN, SEN>;
+  using P = RsPart<T, TN>;
+  constexpr bool FOLD = sizeof(P) > sizeof(T);
   using V = typename Vec4<T>::type;
   constexpr int KQ = kRsRows / 4, LQ = kRsRows + 16 / (int)sizeof(T), BUF = 32 * TN * LQ;
   extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -718,9 +736,9 @@ __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, 
       bo[i] = 16 * (TN + t % TN) * LQ;
     }
   }
-  V acc[C::TPW];
+  typename Vec4<P>::type acc[C::TPW];
 #pragma unroll
-  for (int i = 0; i < C::TPW; ++i) acc[i] = V{0, 0, 0, 0};
+  for (int i = 0; i < C::TPW; ++i) acc[i] = {0, 0, 0, 0};
   const int G = gridDim.x;
   int b = 0, ch = blockIdx.x;
   load_idx(ch);
@@ -740,15 +758,23 @@ __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, 
         if (i == 0 || ao[i] != ao[i - 1]) vload<KQ>(base + ao[i], av);
         T bv[KQ];
         vload<KQ>(base + bo[i], bv);
+        if constexpr (FOLD) {
+          V c = V{0, 0, 0, 0};
 #pragma unroll
-        for (int u = 0; u < KQ; ++u) acc[i] = mfma4(av[u], bv[u], acc[i]);
+          for (int u = 0; u < KQ; ++u) c = mfma4(av[u], bv[u], c);
+#pragma unroll
+          for (int v = 0; v < 4; ++v) acc[i][v] += (double)c[v];
+        } else {
+#pragma unroll
+          for (int u = 0; u < KQ; ++u) acc[i] = mfma4(av[u], bv[u], acc[i]);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);  // one tile's operands at a time
     }
   }
   __syncthreads();
   if (tid == 0) errw[blockIdx.x] = bad;
-  T* out = part + ((size_t)blockIdx.x * C::NT + t0) * 256;
+  P* out = part + ((size_t)blockIdx.x * C::NT + t0) * 256;
 #pragma unroll
   for (int i = 0; i < C::TPW; ++i)
     if (t0 + i < C::NT)
@@ -756,17 +782,17 @@ __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, 
       for (int v = 0; v < 4; ++v) out[i * 256 + frag_row<T>(lk, v) * 16 + lr] = acc[i][v];
 }
 
-// The sums of k_red_stream's parts: G (rows of stride LG, both triangles;
+// The sums of k_red_stream's parts (element type P): G (rows of stride LG, both triangles;
 // only N x N is written) and B, I added, or, SEN, the update's Wt[b][a] (NP x
 // NP, zero outside N x N; zeros to iters0).  A workgroup takes 32 threads of
 // 16 consecutive bytes of a tile, eight times: thread row sub adds the parts
 // sub, sub + 8, .. in order, then the eight are added in order.
-template <typename T, bool SEN>
+template <typename T, typename P, bool SEN>
 __global__ __launch_bounds__(kBlock) void k_red_sum_tiles(int N, int TN, int LG, int S,
-                                                          const T* part, double* Gp, double* B,
+                                                          const P* part, double* Gp, double* B,
                                                           T* Wt, int NP, const int* errw, int nerr,
                                                           int* err, int* iters0) {
-  constexpr int VU = 16 / (int)sizeof(T);
+  constexpr int VU = 16 / (int)sizeof(P);
   __shared__ double red[8][32][VU];
   const int tid = threadIdx.x, x = tid & 31, sub = tid >> 5;
   if (blockIdx.x == 0) {
@@ -787,13 +813,13 @@ __global__ __launch_bounds__(kBlock) void k_red_sum_tiles(int N, int TN, int LG,
   const int ntl = SEN ? 0 : TN * (TN + 1) / 2, nt = ntl + TN * TN;
   const int e0 = (blockIdx.x * 32 + x) * VU;  // first element (grid: nt * 256 / (32 VU))
   int t = e0 / 256, ti = 0, tj;
-  const T* src = part + e0;
+  const P* src = part + e0;
   double acc[VU];
 #pragma unroll
   for (int v = 0; v < VU; ++v) acc[v] = 0.0;
 #pragma unroll 8
   for (int s = sub; s < S; s += 8) {
-    T v[VU];
+    P v[VU];
     vload<VU>(src + (size_t)s * nt * 256, v);
 #pragma unroll
     for (int u = 0; u < VU; ++u) acc[u] += (double)v[u];
@@ -1450,25 +1476,25 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
   return hipGetLastError();
 }
 
-int reduced_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
+int reduced_shape(int m, int N, int esz, int* NP, int* mpad, int* KC, int* S) {
   if (N < 2 || N > 128 || m < 1 || m > (1 << 30)) return 0;
   static_assert(kRedFusedRows == kRsRows, "one chunk height");
   const int nch = (m + kRsRows - 1) / kRsRows;
   *NP = N <= 32 ? 32 : N <= 64 ? 64 : 128;
   *KC = kRsRows;
-  *S = red_streamed(m, N) && nch > kRsGroups ? kRsGroups : nch;
+  *S = red_streamed(m, N) ? red_stream_groups(m, N, esz) : nch;
   *mpad = nch * kRsRows;
   return 1;
 }
 
-// 16 x 16 tiles of the product a part holds: all of NP x 2NP from k_red_pg.
-size_t reduced_part_elems(int m, int N) {
+// A part holds all of NP x 2NP from k_red_pg, else its 16 x 16 tiles (RsPart).
+size_t reduced_part_bytes(int m, int N, int esz) {
   if (!red_streamed(m, N)) {
     const size_t np = N <= 32 ? 32 : 64;
-    return np * 2 * np;
+    return np * 2 * np * esz;
   }
   const size_t tn = red_stream_tiles(N);
-  return (tn * (tn + 1) / 2 + tn * tn) * 256;
+  return (tn * (tn + 1) / 2 + tn * tn) * 256 * (tn <= 4 ? sizeof(double) : esz);
 }
 
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
@@ -1530,33 +1556,48 @@ hipError_t launch_red_update_np(int n, int N, const T* Xf, T* Xa, const T* Wt, h
   return launch_red_update<T, NP, 16>(n, N, Xf, Xa, Wt, s);
 }
 
+// The two launches of a streamed product: the parts, then their sums (B null: the
+// sEnKF's, into Wt).
 template <typename T, int TN, bool SEN>
-hipError_t launch_red_stream_tn(int n, int m, int N, int k, int S, const T* Xg, const int32_t* idx,
-                                const T* hw, const T* y, const T* rdiag, const T* eps, T* part,
-                                int* errw, hipStream_t s) {
+hipError_t launch_red_stream_tn(int n, int m, int N, int k, const T* Xg, const int32_t* idx,
+                                const T* hw, const T* y, const T* rdiag, const T* eps, void* ws,
+                                const Layout& L, int* iters0, hipStream_t s) {
+  using P = RsPart<T, TN>;
+  using C = RsCfg<TN, SEN>;
+  unsigned char* base = (unsigned char*)ws;
+  P* part = (P*)(base + L.rpart);
+  int* errw = (int*)(base + L.rerr);
   constexpr size_t lds = red_stream_lds<T, TN>();
-  const hipError_t e = hipFuncSetAttribute((const void*)k_red_stream<T, TN, SEN>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  hipError_t e = hipFuncSetAttribute((const void*)k_red_stream<T, TN, SEN>,
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_red_stream<T, TN, SEN>), dim3(S), dim3(kRsThreads), lds, s, n, m, N, k,
+  hipLaunchKernelGGL((k_red_stream<T, TN, SEN>), dim3(L.rS), dim3(kRsThreads), lds, s, n, m, N, k,
                      (m + kRsRows - 1) / kRsRows, Xg, idx, hw, y, rdiag, eps, part, errw);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL((k_red_sum_tiles<T, P, SEN>), dim3(C::NT * 8 * sizeof(P) / 16), dim3(kBlock),
+                     0, s, N, TN, L.rNP < 64 ? 64 : L.rNP, L.rS, (const P*)part,
+                     SEN ? nullptr : (double*)(base + L.rG), SEN ? nullptr : (double*)(base + L.rB),
+                     SEN ? (T*)(base + L.rWt) : nullptr, L.rNP, (const int*)errw, L.rS,
+                     (int*)(base + L.err), iters0);
   return hipGetLastError();
 }
 template <typename T, bool SEN>
-hipError_t launch_red_stream(int n, int m, int N, int k, int S, const T* Xg, const int32_t* idx,
-                             const T* hw, const T* y, const T* rdiag, const T* eps, T* part,
-                             int* errw, hipStream_t s) {
+hipError_t launch_red_stream(int n, int m, int N, int k, const T* Xg, const int32_t* idx,
+                             const T* hw, const T* y, const T* rdiag, const T* eps, void* ws,
+                             const Layout& L, int* iters0, hipStream_t s) {
   auto one = [&](auto tn) {
-    return launch_red_stream_tn<T, decltype(tn)::value, SEN>(n, m, N, k, S, Xg, idx, hw, y, rdiag,
-                                                             eps, part, errw, s);
+    return launch_red_stream_tn<T, decltype(tn)::value, SEN>(n, m, N, k, Xg, idx, hw, y, rdiag,
+                                                             eps, ws, L, iters0, s);
   };
-  if (N <= 32) return one(std::integral_constant<int, 2>{});
-  if (N <= 48) return one(std::integral_constant<int, 3>{});
-  if (N <= 64) return one(std::integral_constant<int, 4>{});
-  if (N <= 80) return one(std::integral_constant<int, 5>{});
-  if (N <= 96) return one(std::integral_constant<int, 6>{});
-  if (N <= 112) return one(std::integral_constant<int, 7>{});
-  return one(std::integral_constant<int, 8>{});
+  switch (red_stream_tiles(N)) {
+    case 2: return one(std::integral_constant<int, 2>{});
+    case 3: return one(std::integral_constant<int, 3>{});
+    case 4: return one(std::integral_constant<int, 4>{});
+    case 5: return one(std::integral_constant<int, 5>{});
+    case 6: return one(std::integral_constant<int, 6>{});
+    case 7: return one(std::integral_constant<int, 7>{});
+    default: return one(std::integral_constant<int, 8>{});
+  }
 }
 
 template <typename T, int NP>
@@ -1577,13 +1618,9 @@ hipError_t launch_reduced_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, c
   const int LG = NP < 64 ? 64 : NP, RPL = LG / 64, NR = LG;
   hipError_t e;
   if (red_streamed(m, N)) {
-    if ((e = launch_red_stream<T, false>(ng, m, N, k, L.rS, Xg, idx, hw, y, rdiag, eps, part, errw,
+    if ((e = launch_red_stream<T, false>(ng, m, N, k, Xg, idx, hw, y, rdiag, eps, ws, L, nullptr,
                                          s)) != hipSuccess)
       return e;
-    const int tn = red_stream_tiles(N), nt = tn * (tn + 1) / 2 + tn * tn;
-    hipLaunchKernelGGL((k_red_sum_tiles<T, false>), dim3(nt * 8 * sizeof(T) / 16), dim3(kBlock), 0,
-                       s, N, tn, LG, L.rS, (const T*)part, Gp, B, (T*)nullptr, NP,
-                       (const int*)errw, L.rS, err, (int*)nullptr);
   } else if constexpr (NP <= 64) {
     hipLaunchKernelGGL((k_red_pg<T, NP, false>), dim3(L.rS), dim3(kBlock), 0, s, ng, m, N, k, Xg,
                        idx, hw, y, rdiag, eps, part, errw);
@@ -1698,13 +1735,9 @@ hipError_t launch_senkf_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, con
   T* Wt = (T*)(base + L.rWt);
   hipError_t e;
   if (red_streamed(m, N)) {
-    if ((e = launch_red_stream<T, true>(n, m, N, k, L.rS, Xf, idx, hw, y, rdiag, eps, part, errw,
+    if ((e = launch_red_stream<T, true>(n, m, N, k, Xf, idx, hw, y, rdiag, eps, ws, L, iters0,
                                         s)) != hipSuccess)
       return e;
-    const int tn = red_stream_tiles(N);
-    hipLaunchKernelGGL((k_red_sum_tiles<T, true>), dim3(tn * tn * 8 * sizeof(T) / 16), dim3(kBlock),
-                       0, s, N, tn, 0, L.rS, (const T*)part, (double*)nullptr, (double*)nullptr, Wt,
-                       NP, (const int*)errw, L.rS, err, iters0);
   } else if constexpr (NP <= 64) {
     hipLaunchKernelGGL((k_red_pg<T, NP, true>), dim3(L.rS), dim3(kBlock), 0, s, n, m, N, k, Xf,
                        idx, hw, y, rdiag, eps, part, errw);
