@@ -284,7 +284,11 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
 // and S parts of it (esz: bytes per value).  0 when N is out of range.
 int reduced_shape(int m, int N, int esz, int* NP, int* mpad, int* KC, int* S);
 size_t reduced_part_bytes(int m, int N, int esz);  // one chunk's (or workgroup's) part
-// The same for N > 128: NP a multiple of 64, mpad, KC and S as above.
+// The same for N > 128: NP a multiple of 64, KC and S as above, mpad rows of Q, which
+// takes kRedPanel rows at a time.  The reduced mode's partial sums without Q held 1024
+// N x 2N parts at most, 16 N^2 KiB: more than a panel of 2^16 rows and its parts for
+// every N > 128, and a panel's launches are then long (268 MB of Q at N = 200).
+constexpr int kRedPanel = 1 << 16;
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
 // Xg (ng rows) is the array the observations are gathered from; Xf is
 // updated (the same unless R is not diagonal)

@@ -1107,23 +1107,26 @@ __global__ __launch_bounds__(kBlock) void k_red_update(int n, int N, const T* Xf
 // ---------------------------------------------------------------------------
 // Reduced mode and sEnKF for N > 128, in FP64 whatever T is: NP = N rounded up
 // to 64, Q (mpad x 2NP, as above, in double) through memory, the product on
-// the FP64 MFMA in 64 x 64 tiles over row chunks.  (One workgroup per row
+// the FP64 MFMA in 64 x 64 tiles over row chunks.  Past kRedPanel rows Q holds one
+// panel of rows at a time, so that the workspace stops growing there.  (One workgroup per row
 // block with a scalar FP64 sum per output, and a serial sum over up to 1024
 // N x 2N parts, took 277 + 88 us at m = 5003, N = 200.)
 // ---------------------------------------------------------------------------
 
-// Row i of Q, one wave per row.  HX is kept in the row's left half until its
-// mean is known.  errw: an error word per workgroup; SEN: the sEnKF's row scale.
+// Row i of Q (in row i - p0 of the panel that starts at p0), one wave per row.  HX is
+// kept in the row's left half until its mean is known.  errw: an error word per
+// workgroup, kept over the panels; SEN: the sEnKF's row scale.
 template <typename T, bool SEN>
-__global__ __launch_bounds__(kBlock) void k_red_prep_wide(int n, int m, int N, int NP, int k,
-                                                          const T* Xf, const int32_t* idx,
+__global__ __launch_bounds__(kBlock) void k_red_prep_wide(int n, int m, int p0, int N, int NP,
+                                                          int k, const T* Xf, const int32_t* idx,
                                                           const T* hw, const T* y, const T* rdiag,
                                                           const T* eps, double* Q, int* errw) {
   __shared__ int bad;
-  const int lane = threadIdx.x & 63, i = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (threadIdx.x == 0) bad = 0;
+  const int lane = threadIdx.x & 63, row = blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  const int i = p0 + row;
+  if (threadIdx.x == 0) bad = p0 > 0 ? errw[blockIdx.x] : 0;
   __syncthreads();
-  double* qr = Q + (size_t)i * 2 * NP;
+  double* qr = Q + (size_t)row * 2 * NP;
   const bool live = i < m;
   constexpr int U = 4;
   double sum = 0.0;
@@ -1170,12 +1173,13 @@ __global__ __launch_bounds__(kBlock) void k_red_prep_wide(int n, int m, int N, i
   if (threadIdx.x == 0) errw[blockIdx.x] = bad;
 }
 
-// part[s] = Q[rows of chunk s, :NP]^T Q[rows of chunk s, :], tiles t0 .. of
-// the tile list (all of the right half, the left half's lower tiles skipped).  All tiles of a chunk run on one XCD
+// part[s] = Q[rows of chunk s, :NP]^T Q[rows of chunk s, :] of a panel of mpad rows
+// (add: onto the panels before it), tiles t0 .. of the tile list (all of the right
+// half, the left half's lower tiles skipped).  All tiles of a chunk run on one XCD
 // (workgroup w runs on XCD w mod 8), whose L2 then serves the chunk's rows to
 // every tile after the first.
 __global__ __launch_bounds__(kBlock) void k_red_gemm_wide(int NP, int KC, int mpad, int S, int t0,
-                                                          int ntile, const double* Q,
+                                                          int ntile, int add, const double* Q,
                                                           double* part) {
   constexpr int MB = 2, HS = 32;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, lr = lane & 15, lk = lane >> 4;
@@ -1193,12 +1197,19 @@ __global__ __launch_bounds__(kBlock) void k_red_gemm_wide(int NP, int KC, int mp
   }
   const int ca = ta * 64 + (wv >> 1) * HS + lr, cb = tb * 64 + (wv & 1) * HS + lr;
   const int r0 = chunk * KC, r1 = min(mpad, r0 + KC);
+  if (r0 >= r1) return;  // (a last, shorter panel)
   const size_t QW = 2 * (size_t)NP;
+  double* out = part + (size_t)chunk * NP * QW;
+  auto at = [&](int x, int z, int i) {
+    return (size_t)(ca - lr + 16 * x + frag_row<double>(lk, i)) * QW + cb + 16 * z;
+  };
   v4d acc[MB][MB];
 #pragma unroll
   for (int x = 0; x < MB; ++x)
 #pragma unroll
-    for (int z = 0; z < MB; ++z) acc[x][z] = v4d{0.0, 0.0, 0.0, 0.0};
+    for (int z = 0; z < MB; ++z)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[x][z][i] = add ? out[at(x, z, i)] : 0.0;
   double an[4][MB], bn[4][MB];
   auto load = [&](int r) {
 #pragma unroll
@@ -1229,14 +1240,12 @@ __global__ __launch_bounds__(kBlock) void k_red_gemm_wide(int NP, int KC, int mp
 #pragma unroll
         for (int z = 0; z < MB; ++z) acc[x][z] = mfma4(ac[u][x], bc[u][z], acc[x][z]);
   }
-  double* out = part + (size_t)chunk * NP * QW;
 #pragma unroll
   for (int x = 0; x < MB; ++x)
 #pragma unroll
     for (int z = 0; z < MB; ++z)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        out[(size_t)(ca - lr + 16 * x + frag_row<double>(lk, i)) * QW + cb + 16 * z] = acc[x][z][i];
+      for (int i = 0; i < 4; ++i) out[at(x, z, i)] = acc[x][z][i];
 }
 
 // G = I + sum_s part_s[:, :NP] (from its upper tiles; stride LG, rows and
@@ -1499,7 +1508,7 @@ size_t reduced_part_bytes(int m, int N, int esz) {
 
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
   const int np = (N + 63) / 64 * 64, TT = np / 64, tiles = TT * (TT + 1) / 2 + TT * TT;
-  const long mp = ((long)m + 31) / 32 * 32, blocks = mp / 32;
+  const long mp = ((long)(m < kRedPanel ? m : kRedPanel) + 31) / 32 * 32, blocks = mp / 32;
   // about 512 workgroups, in whole rounds over the eight XCDs, chunks of at
   // least 64 rows
   long sc = (512 / tiles + 7) / 8 * 8;
@@ -1665,14 +1674,19 @@ hipError_t red_wide_product(int ng, int m, int N, int k, const T* Xg, const int3
   double* part = (double*)(base + L.rpart);
   int* errw = (int*)(base + L.rerr);
   const int NP = L.rWNP, nprep = L.rmpad / (kBlock / 64), TT = NP / 64, NTG = TT * (TT + 1) / 2;
-  hipLaunchKernelGGL((k_red_prep_wide<T, SEN>), dim3(nprep), dim3(kBlock), 0, s, ng, m, N, NP, k,
-                     Xg, idx, hw, y, rdiag, eps, Q, errw);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int t0 = SEN ? NTG : 0, ntile = NTG + TT * TT - t0;
-  hipLaunchKernelGGL(k_red_gemm_wide, dim3(8 * ntile * ((L.rS + 7) / 8)), dim3(kBlock), 0, s, NP,
-                     L.rKC, L.rmpad, L.rS, t0, ntile, (const double*)Q, part);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipError_t e;
+  for (long at = 0; at < m; at += kRedPanel) {
+    const int p0 = (int)at, rows = m - p0 < kRedPanel ? m - p0 : kRedPanel;
+    const int mpad = (rows + 31) / 32 * 32;
+    const int KC = p0 == 0 ? L.rKC : (mpad / 32 + L.rS - 1) / L.rS * 32;  // all parts busy
+    hipLaunchKernelGGL((k_red_prep_wide<T, SEN>), dim3(mpad / (kBlock / 64)), dim3(kBlock), 0, s,
+                       ng, m, p0, N, NP, k, Xg, idx, hw, y, rdiag, eps, Q, errw);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_red_gemm_wide, dim3(8 * ntile * ((L.rS + 7) / 8)), dim3(kBlock), 0, s,
+                       NP, KC, mpad, L.rS, t0, ntile, p0 > 0 ? 1 : 0, (const double*)Q, part);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
   const int W = SEN ? NP : 2 * NP;
   hipLaunchKernelGGL(k_red_sum_wide, dim3((NP * W + kBlock - 1) / kBlock), dim3(kBlock), 0, s, N,
                      NP, L.rLG, L.rS, SEN ? 0 : 1, SEN ? 0.0 : 1.0, (const double*)part,
