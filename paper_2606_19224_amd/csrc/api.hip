@@ -87,6 +87,15 @@ inline bool prec_tile(int p) { return p == CGD_FP32 || p == CGD_MIXED_BF16 || p 
 // step grows with m (11 us at m = 1024, 18 us at 2048, 51 us at 4093, N = 100)
 // while the row-block solver's is bound by its exchange (16 to 18 us).
 constexpr int kTile64MinRows = 1800;
+// The column solver then takes up to this many rows, past them the streaming solver,
+// which reads S once a step for all members: 20 steps at N = 72 take 23.6 ms there
+// and 21.1 here at m = 80000, 27.1 and 26.6 at 100000, 34.7 and 40.8 at 130000 (N = 65:
+// 21.6 / 20.7 and 24.3 / 26.7 at 80000 and 100000; N = 88: 43.6 / 42.1 and 51.5 / 53.5
+// at 130000 and 170000; N = 100: 133.8 / 126.1 at 400000, N = 112: 232.9 / 126.4).
+constexpr int columns_wide_max(int N) {
+  return N < 80 ? 80000 : N < 96 ? 130000 : kColumnsMaxRows;
+}
+constexpr int kWideAppendRows = 1024;  // its buffers may lie behind the others' up to here
 
 Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
   Layout L;
@@ -174,25 +183,28 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       if ((size_t)L.splitP * L.splitMs > rows) rows = (size_t)L.splitP * L.splitMs;
       L.gerr = L.xwords ? take(sizeof(int) * (rows / 8 + 1)) : 0;
     }
-    // FP64 column solver past N = 64: no other solver's partials are live with
-    // it, so its buffers lie on partG .. partW when those are large enough
-    // (all but small m, and m past 16 N^2), else behind everything
-    if (prec == CGD_FP64 && N > 64 && N <= 128 && (L.wrows = columns_wide_rows(m)) > 0) {
-      const size_t rows = (size_t)L.wrows, sizes[7] = {
+    // FP64 column solver past N = 64: no other solver's buffers are live with it, so
+    // its own lie on S .. partW when those are large enough, for few rows behind
+    // everything; where they are not (m past about a million) it is not offered
+    if (prec == CGD_FP64 && N > 64 && N <= 128 && m <= columns_wide_max(N)) {
+      const size_t rows = (size_t)columns_wide_rows(m), sizes[7] = {
           sizeof(double) * rows * 128, sizeof(double) * N * rows, sizeof(double) * N * rows,
           sizeof(double) * N * rows,   sizeof(double) * N * rows, sizeof(double) * rows,
           sizeof(int) * (rows / 8 + 1)};
       size_t* offs[7] = {&L.wS, &L.wD, &L.wZ, &L.wR, &L.wP, &L.wRp, &L.wgerr};
       size_t need = 0;
       for (size_t b : sizes) need += al256(b);
-      size_t at = L.partG;
-      if (need > L.col - L.partG) {
+      size_t at = L.S;
+      if (need > L.col - L.S && m <= kWideAppendRows) {
         at = o;
         o += need;
       }
-      for (int q = 0; q < 7; ++q) {
-        *offs[q] = at;
-        at += al256(sizes[q]);
+      if (at != L.S || need <= L.col - L.S) {
+        L.wrows = (int)rows;
+        for (int q = 0; q < 7; ++q) {
+          *offs[q] = at;
+          at += al256(sizes[q]);
+        }
       }
       int ng = 0, nb = 0;
       if (m >= kTile64MinRows && tile64_shape(m, N, &ng, &nb)) {
@@ -1364,7 +1376,7 @@ int cgd_layout_selfcheck(int n, int m, int N, int k, int prec) {
   // the partials or the workspace and leave the results alone
   if (L.wrows > 0) {
     const size_t rows = (size_t)L.wrows, end = L.wgerr + sizeof(int) * (rows / 8 + 1);
-    if (L.wS < L.partG || end > L.total || (L.wS < L.col && end > L.col)) ++bad;
+    if (L.wS < L.S || end > L.total || (L.wS < L.col && end > L.col)) ++bad;
     if (L.wrows < m || L.wD - L.wS < 8 * rows * 128 || L.wZ - L.wD < 8 * N * rows ||
         L.wR - L.wZ < 8 * N * rows || L.wP - L.wR < 8 * N * rows ||
         L.wRp - L.wP < 8 * N * rows || L.wgerr - L.wRp < 8 * rows)
