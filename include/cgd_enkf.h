@@ -144,7 +144,10 @@ typedef struct {
                              at once or refuses the launch; slower per call)   */
   unsigned census_ticks;  /* the census's wait in 100 MHz ticks, 0 = 100000
                              (1 ms); a tiny value forces the CGD_ERR_BUSY path
-                             (tests)                                           */
+                             (tests).  The FP64 row-block solver has no census:
+                             the limit of each of its waits, 0 = 30 s in the
+                             first exchange, then 1 s (CGD_ERR_HIP, X_a left
+                             as it was)                                        */
 } cgd_tuning;
 
 typedef struct {

@@ -518,12 +518,13 @@ cgd_status run_full(int n, int m, int N, int k, const void* Xf, void* Xa, const 
   hipEvent_t* ev = (hipEvent_t*)o.prof_events;
   if constexpr (sizeof(T) == 8) {
     if (sc.kind == 5) {
+      a.census_ticks = o.census_ticks;
       if (launch_cg_tile64(a, L.t64NG, L.t64nblk, (unsigned long long*)(b + L.t64x),
                            (double*)(b + L.t64S), a.D, (double*)(b + L.t64rv), ev, s) !=
           hipSuccess)
         return CGD_ERR_HIP;
       if (ev && hipEventRecord(ev[1], s) != hipSuccess) return CGD_ERR_HIP;
-      if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, nullptr) != hipSuccess)
+      if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, a.err) != hipSuccess)
         return CGD_ERR_HIP;
       return unscale_z_out<T>(m, N, r, o, s);
     }
@@ -582,8 +583,7 @@ cgd_status run_full(int n, int m, int N, int k, const void* Xf, void* Xa, const 
       if (launch_cg_tile(a, sc.NP, sc.RB, variant, s) != hipSuccess)
         return CGD_ERR_HIP;
       if (ev && hipEventRecord(ev[1], s) != hipSuccess) return CGD_ERR_HIP;
-      if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s,
-                           a.census ? a.err : nullptr) != hipSuccess)
+      if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, a.err) != hipSuccess)
         return CGD_ERR_HIP;
       return unscale_z_out<T>(m, N, r, o, s);
     }
@@ -604,8 +604,7 @@ cgd_status run_full(int n, int m, int N, int k, const void* Xf, void* Xa, const 
     if (launch_cg_solve<T>(a, sc.nwg, s) != hipSuccess) return CGD_ERR_HIP;
   }
   if (ev && hipEventRecord(ev[1], s) != hipSuccess) return CGD_ERR_HIP;
-  if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, a.census ? a.err : nullptr) !=
-      hipSuccess)
+  if (launch_update<T>(n, N, (const T*)Xf, (T*)Xa, a.Wd, 0, s, a.err) != hipSuccess)
     return CGD_ERR_HIP;
   return unscale_z_out<T>(m, N, r, o, s);
 }

@@ -14,7 +14,9 @@
 // the same decisions from the same bits; W = sum_k alpha_k G_k in double.
 //
 // Always launched cooperatively (the workgroups wait for each other); every
-// wait is bounded by 1 s.
+// wait is bounded: by 1 s, and in the first exchange, where a workgroup may still be
+// waiting for a CU that another stream's kernel holds, by 30 s (the streaming
+// solver, which these sizes would run otherwise, waits for that without a bound).
 //
 // Bound: the exchange (33 KiB out and in per workgroup and step) and 3.4 us of
 // FP64 MFMA a step.  16 members a group rather than 32 keep both the
@@ -39,6 +41,7 @@ constexpr int kGW = kNP * kM;     // doubles of S^T r
 constexpr int kEx = kGW + 4 * kM; // doubles of an exchange: S^T r, four sums per member
 constexpr int kSlot = 2 * 2 * kEx;  // words per workgroup (two exchanges alternate)
 constexpr int kBatch64 = 12;      // owner step: partials in flight per thread
+constexpr unsigned long long kFirstWaitTicks = 30 * kTileWaitTicks;
 
 struct __align__(16) T64Lds {
   double S[kRows * kLd];
@@ -52,6 +55,7 @@ struct __align__(16) T64Lds {
 struct Tile64Args {
   int N, m, NG, nblk, maxit, want_relres;
   double tol;
+  unsigned long long ticks;  // every wait's limit, 0 = kFirstWaitTicks, then kTileWaitTicks
   unsigned long long* txp;  // NG * nblk * kSlot
   unsigned long long* txr;  // NG * kSlot
   const double* S;          // m x kNP
@@ -108,6 +112,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_tile64(Tile64Args a) {
       p[t][i] = 0.0;
     }
 
+  unsigned long long ticks = a.ticks ? a.ticks : kFirstWaitTicks;  // this exchange's limit
   // the four sums of this wave's rows into L.xs
   auto row_sums = [&]() {
     double v[4] = {0.0, 0.0, 0.0, 0.0};
@@ -182,7 +187,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_tile64(Tile64Args a) {
     bool bad = false;
     for (int q = tid; q < nblk && Ld > 0; q += kBlock) {
       const unsigned long long* w = base + (size_t)q * kSlot + 2 * dlo;
-      poll64(w, ep, ld64(w), bad);
+      poll64(w, ep, ld64(w), bad, ticks);
     }
     if (__syncthreads_or(bad)) return false;
     for (int d0 = 0; d0 < Ld; d0 += kBlock) {
@@ -203,8 +208,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_tile64(Tile64Args a) {
           for (int u = 0; u < kBatch64; ++u)
             if (q + u < q1) {
               const unsigned long long* pw = w0 + (size_t)(q + u) * kSlot;
-              const unsigned long long lo = poll64(pw, ep, w[u][0], bad);
-              const unsigned long long hi = poll64(pw + 1, ep, w[u][1], bad);
+              const unsigned long long lo = poll64(pw, ep, w[u][0], bad, ticks);
+              const unsigned long long hi = poll64(pw + 1, ep, w[u][1], bad, ticks);
               s += to_dbl(lo, hi);
             }
         }
@@ -244,7 +249,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_tile64(Tile64Args a) {
 #pragma unroll
     for (int u = 0; u < 18; ++u)
       if (u < nw) w[u] = ld64(at(u));
-    poll_all(w, nw, at, ep, bad);
+    poll_all(w, nw, at, ep, bad, ticks);
     if (tid < 4 * kM) L.sums[tid] = to_dbl(w[16], w[17]);
     if (__syncthreads_or(bad)) {
       bad = true;
@@ -313,6 +318,7 @@ __global__ __launch_bounds__(kBlock) void k_cg_tile64(Tile64Args a) {
           r[t][i] -= alpha * q;
         }
     ++ep;
+    if (kit == 0) ticks = a.ticks ? a.ticks : kTileWaitTicks;
     bad = !exchange(ep);
   }
   if (bad) {
@@ -374,8 +380,8 @@ __global__ __launch_bounds__(kBlock) void k_cg_tile64(Tile64Args a) {
   double tot = 0.0;
   for (int q = tid / kM; q < nblk; q += kBlock / kM) {
     const unsigned long long* w = gpart + (size_t)q * kSlot + (size_t)(er & 1) * 2 * kEx + 2 * lr;
-    const unsigned long long lo = poll64(w, er, ld64(w), bad);
-    const unsigned long long hi = poll64(w + 1, er, ld64(w + 1), bad);
+    const unsigned long long lo = poll64(w, er, ld64(w), bad, ticks);
+    const unsigned long long hi = poll64(w + 1, er, ld64(w + 1), bad, ticks);
     tot += to_dbl(lo, hi);
   }
   L.own[tid] = tot;
@@ -480,6 +486,7 @@ hipError_t launch_cg_tile64(const CGArgs<double>& a, int NG, int nblk, unsigned 
   t.maxit = a.maxit;
   t.want_relres = a.want_relres;
   t.tol = a.tol;
+  t.ticks = a.census_ticks;
   t.txp = words;
   t.txr = words + (size_t)kSlot * NG * nblk;
   t.S = S;

@@ -117,16 +117,17 @@ __device__ inline void st64(unsigned long long* p, unsigned v, unsigned ep) {
 constexpr unsigned long long kTileWaitTicks = 100000000ull;
 
 // Re-reads *p until its exchange number is ep (w: the first read); a wait
-// that runs out sets bad, and once bad is set no wait starts.
+// that runs out (ticks) sets bad, and once bad is set no wait starts.
 __device__ inline unsigned long long poll64(const unsigned long long* p, unsigned ep,
-                                            unsigned long long w, bool& bad) {
+                                            unsigned long long w, bool& bad,
+                                            unsigned long long ticks = kTileWaitTicks) {
   if ((unsigned)(w >> 32) == ep || bad) return w;
   const unsigned long long t0 = __builtin_amdgcn_s_memrealtime();
   for (;;) {
     __builtin_amdgcn_s_sleep(1);
     w = ld64(p);
     if ((unsigned)(w >> 32) == ep) break;
-    if (__builtin_amdgcn_s_memrealtime() - t0 > kTileWaitTicks) {
+    if (__builtin_amdgcn_s_memrealtime() - t0 > ticks) {
       bad = true;
       break;
     }
@@ -139,7 +140,8 @@ __device__ inline unsigned long long poll64(const unsigned long long* p, unsigne
 // sets bad, and once bad is set no wait starts.
 template <int NMAX, typename At>
 __device__ __attribute__((always_inline)) void poll_all(unsigned long long (&w)[NMAX], int n, At at,
-                                                        unsigned ep, bool& bad) {
+                                                        unsigned ep, bool& bad,
+                                                        unsigned long long ticks = kTileWaitTicks) {
   unsigned long long t0 = 0;
   for (;;) {
     bool stale = false;
@@ -149,7 +151,7 @@ __device__ __attribute__((always_inline)) void poll_all(unsigned long long (&w)[
     const unsigned long long now = __builtin_amdgcn_s_memrealtime();
     if (t0 == 0) {
       t0 = now;
-    } else if (now - t0 > kTileWaitTicks) {
+    } else if (now - t0 > ticks) {
       bad = true;
       return;
     }

@@ -210,7 +210,8 @@ hipError_t launch_cg_columns_wide(const CGArgs<double>& a, double* Sp, double* V
 // Row-block x member-group solver in FP64 (cg_tile64.hip), 64 < N <= 128,
 // cold start: members in groups of 16, 128 rows per workgroup, NG * nblk
 // workgroups that must run at once (always a cooperative launch).  words:
-// tile64_words of exchange words, S: m x 128, D: m x N, rv: m.
+// tile64_words of exchange words, S: m x 128, D: m x N, rv: m.  Its waits give up
+// after a.census_ticks, 0 for their own limits.
 int tile64_shape(int m, int N, int* NG, int* nblk);
 size_t tile64_words(int NG, int nblk);
 int tile64_coresident();
@@ -275,7 +276,9 @@ hipError_t launch_batched(const BProb<T>* probs, const int2* gtab, int ngather,
 template <typename T>
 hipError_t launch_unscale_rows(int m, int N, T* z, const T* rdiag, hipStream_t s);
 // X_a from W (mode 0: X_f + A W, mode 1: X_f W); with `skip`, the launch
-// writes nothing when bit 2 of *skip is set.
+// writes nothing when *skip has a bit of kErrNoW: a solver's error word whose wait
+// for other workgroups (bit 0) or start-up census (bit 2) gave up before W was formed.
+constexpr int kErrNoW = 1 | 4;
 template <typename T>
 hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int mode,
                          hipStream_t s, const int* skip = nullptr);

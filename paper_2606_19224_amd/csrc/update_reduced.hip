@@ -12,13 +12,13 @@ namespace {
 // X_a = X_f + A W  (mode 0, Algorithm 1 with W = S^T Z/(N-1), A = X_f - xbar 1^T)
 // X_a = X_f W      (mode 1, Algorithm 2)
 // Each workgroup owns RBX whole rows: it stages them in LDS before writing,
-// so X_a may alias X_f.  With `skip`, nothing is written when bit 2 of *skip
-// is set (the solver's start-up census gave up: W was never formed).
+// so X_a may alias X_f.  With `skip`, nothing is written when *skip has a bit of
+// kErrNoW (W was never formed).
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_update(int n, int N, int RBX, const T* Xf, T* Xa,
                                                    const double* Wd, int mode, const int* skip) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if (skip && (*skip & 4)) return;
+  if (skip && (*skip & kErrNoW)) return;
   double* tile = (double*)smem_raw;  // RBX * N
   double* mean = tile + (size_t)RBX * N;
   const int tid = threadIdx.x;
@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kWideBlock) void k_update_wide(int n, int N, const 
                                                             const int* skip) {
   constexpr int RB = 16 * RT;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if (skip && (*skip & 4)) return;
+  if (skip && (*skip & kErrNoW)) return;
   const int TJ = (N + 15) / 16, KQ = 4 * TJ, LD = 16 * TJ + 2;
   double* As = (double*)smem_raw;  // RB x LD: A', zero past n and N
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, lr = lane & 15, lk = lane >> 4;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(kBlock) void k_update_mfma(int n, int N, const T* X
                                                         const int* skip) {
   using C = UCfg<T, NP>;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if (skip && (*skip & 4)) return;
+  if (skip && (*skip & kErrNoW)) return;
   T* Wt = (T*)smem_raw;
   T* As = Wt + (size_t)NP * C::LD;
   T* Xr = As + (size_t)C::RBX * C::LD;
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(64 * kUpdWaves) void k_update_rows(int n, int N, in
   using U = UCfg<T, NP>;
   constexpr int VU = 16 / (int)sizeof(T), BS = 64 * kUpdWaves;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  if (skip && (*skip & 4)) return;
+  if (skip && (*skip & kErrNoW)) return;
   T* Wt = (T*)smem_raw;  // NP x LD
   const int tid = threadIdx.x, wv = tid >> 6;
   if constexpr (WT) {
