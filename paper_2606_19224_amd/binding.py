@@ -407,7 +407,7 @@ class CProblem(ctypes.Structure):
 class BatchPlan(ctypes.Structure):
     _fields_ = [("count", ctypes.c_int), ("prec", ctypes.c_int), ("n_gather", ctypes.c_int),
                 ("n_solve", ctypes.c_int), ("n_update", ctypes.c_int),
-                ("off_desc", ctypes.c_size_t), ("off_gtab", ctypes.c_size_t),
+                ("members", ctypes.c_int), ("off_desc", ctypes.c_size_t), ("off_gtab", ctypes.c_size_t),
                 ("off_stab", ctypes.c_size_t), ("off_utab", ctypes.c_size_t),
                 ("off_prefix", ctypes.c_size_t), ("off_coli", ctypes.c_size_t),
                 ("ws_bytes", ctypes.c_size_t)]

@@ -716,6 +716,7 @@ struct BatchLayout {
   size_t hdr, desc, gtab, stab, utab, prefix, coli, col, total;
   std::vector<size_t> Sp, Dt, Vz, Vr, Vp, Rp, Wd;
   std::vector<int> NP, mp, RL, gr, ur;
+  int members;  // per solve workgroup: 1, or 4 (FP32)
   int ngather, nsolve, nupdate;
   long long sumN;
 };
@@ -739,7 +740,57 @@ bool batch_problem_ok(const cgd_problem& q) {
   return q.X_f && q.X_a && q.idx && q.w && q.y && q.r_diag;
 }
 
-bool batch_shape(int prec, int m, int N, int* NP, int* mp, int* RL) {
+// Problems in decreasing order of cost (m NP N: a row pass's cost times the iteration
+// bound N, so that the longest solves start first), each on the XCD with the least so far.
+constexpr int kXcd = 8, kXcdCus = 32;
+void batch_xcds(const std::vector<double>& cost, std::vector<int>* order, std::vector<int>* xcd) {
+  const int count = (int)cost.size();
+  order->resize(count);
+  xcd->resize(count);
+  for (int b = 0; b < count; ++b) (*order)[b] = b;
+  std::stable_sort(order->begin(), order->end(), [&](int x, int y) { return cost[x] > cost[y]; });
+  double load[kXcd] = {};
+  for (int b : *order) {
+    int x = 0;
+    for (int t = 1; t < kXcd; ++t)
+      if (load[t] < load[x]) x = t;
+    (*xcd)[b] = x;
+    load[x] += cost[b];
+  }
+}
+
+// FP32: members per solve workgroup.  A group of four (cg_batched.hip) reads S once
+// for its members and takes a quarter of the workgroups, but lasts up to twice as long
+// as one member's own, which has its rows of S in LDS: groups lose where the members
+// run in one round, at most 32 on every XCD, with more than 256 rows (whole call, 8
+// Lorenz-96 filters of N = 16, one member a workgroup against four: m = 256 47.0 / 47.9
+// us, 512 40.9 / 48.8, 2048 53 / 82, 8192 132 / 231; N = 32: 67.0 / 65.4, 59 / 68, 84 /
+// 119, 176 / 276).  In two rounds groups win or are even (16 filters of N = 32: 103 / 66,
+// 92 / 70, 143 / 133, 340 / 334; 8 of N = 64, which fill two: 137 / 107, 117 / 101, 216 /
+// 211, 580 / 529).
+int batch_members(int count, const cgd_problem* probs) {
+  std::vector<double> cost(count);
+  int most = 0;
+  for (int b = 0; b < count; ++b) {
+    const int m = probs[b].m, N = probs[b].N;
+    if (batched_rows(m) == 0) return 1;
+    cost[b] = (double)m * (N <= 16 ? 16 : N <= 32 ? 32 : 64) * N;
+    most = std::max(most, m);
+  }
+  std::vector<int> order, xcd;
+  batch_xcds(cost, &order, &xcd);
+  long members[kXcd] = {};
+  for (int b = 0; b < count; ++b) members[xcd[b]] += probs[b].N;
+  return most > 256 && *std::max_element(members, members + kXcd) <= kXcdCus ? 1 : 4;
+}
+
+bool batch_shape(int prec, int members, int m, int N, int* NP, int* mp, int* RL) {
+  if (members == 4) {
+    *NP = N <= 16 ? 16 : N <= 32 ? 32 : 64;
+    *mp = batched_rows(m);
+    *RL = 0;
+    return N >= 2 && N <= 64 && *mp > 0;
+  }
   return prec == CGD_FP64 ? batched_shape<double>(m, N, NP, mp, RL) != 0
                           : batched_shape<float>(m, N, NP, mp, RL) != 0;
 }
@@ -759,9 +810,10 @@ bool batch_layout(int count, const cgd_problem* probs, int prec, BatchLayout* ou
   };
   B.ngather = B.nsolve = B.nupdate = 0;
   B.sumN = 0;
+  B.members = prec == CGD_FP64 ? 1 : batch_members(count, probs);
   for (int b = 0; b < count; ++b) {
     int NP = 0, mp = 0, RL = 0;
-    if (!batch_shape(prec, probs[b].m, probs[b].N, &NP, &mp, &RL)) return false;
+    if (!batch_shape(prec, B.members, probs[b].m, probs[b].N, &NP, &mp, &RL)) return false;
     const int gr = batch_gather_rows(probs[b]), ur = batch_update_rows(probs[b]);
     if (gr < 0 || ur < 0) return false;
     B.NP.push_back(NP);
@@ -770,7 +822,7 @@ bool batch_layout(int count, const cgd_problem* probs, int prec, BatchLayout* ou
     B.gr.push_back(gr);
     B.ur.push_back(ur);
     B.ngather += (mp + gr - 1) / gr;
-    B.nsolve += prec == CGD_FP64 ? probs[b].N : batched_groups(probs[b].N);
+    B.nsolve += B.members == 4 ? batched_groups(probs[b].N) : probs[b].N;
     B.nupdate += (probs[b].n + ur - 1) / ur;
     B.sumN += probs[b].N;
   }
@@ -785,12 +837,12 @@ bool batch_layout(int count, const cgd_problem* probs, int prec, BatchLayout* ou
   B.col = take(sizeof(double) * CF_NF * (size_t)B.sumN);
   for (int b = 0; b < count; ++b) {
     const size_t mp = (size_t)B.mp[b], N = (size_t)probs[b].N;
-    // FP32: no z, D lies in r, members in groups of four
-    const bool f64 = prec == CGD_FP64;
-    const size_t cols = f64 ? N : 4 * (size_t)batched_groups(probs[b].N);
+    // groups of four members: no z, D lies in r
+    const bool one = B.members == 1;
+    const size_t cols = one ? N : 4 * (size_t)batched_groups(probs[b].N);
     B.Sp.push_back(take(esz * mp * B.NP[b]));
-    B.Dt.push_back(f64 ? take(esz * mp * N) : 0);
-    B.Vz.push_back(f64 ? take(esz * mp * N) : 0);
+    B.Dt.push_back(one ? take(esz * mp * N) : 0);
+    B.Vz.push_back(one ? take(esz * mp * N) : 0);
     B.Vr.push_back(take(esz * mp * cols));
     B.Vp.push_back(take(esz * mp * cols));
     B.Rp.push_back(take(esz * mp));
@@ -806,13 +858,10 @@ cgd_status batch_prepare(int count, const cgd_problem* probs, void* ws, const Ba
   unsigned char* base = (unsigned char*)ws;
   // member solves ordered by decreasing work per member (m N^2: row pass
   // cost m NP times the iteration bound ~N), so the longest start first
-  std::vector<int> order(count);
-  for (int b = 0; b < count; ++b) order[b] = b;
-  std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-    const double cx = (double)B.mp[x] * B.NP[x] * probs[x].N;
-    const double cy = (double)B.mp[y] * B.NP[y] * probs[y].N;
-    return cx > cy;
-  });
+  std::vector<double> cost(count);
+  for (int b = 0; b < count; ++b) cost[b] = (double)B.mp[b] * B.NP[b] * probs[b].N;
+  std::vector<int> order, xcd;
+  batch_xcds(cost, &order, &xcd);
   std::vector<int> prefix(count + 1, 0);
   for (int b = 0; b < count; ++b) prefix[b + 1] = prefix[b] + probs[b].N;
   std::vector<BProb<T>> desc(count);
@@ -836,24 +885,15 @@ cgd_status batch_prepare(int count, const cgd_problem* probs, void* ws, const Ba
     for (int i0 = 0; i0 < B.mp[b]; i0 += B.gr[b]) gtab.push_back(make_int2(b, i0));
     for (int i0 = 0; i0 < q.n; i0 += B.ur[b]) utab.push_back(make_int2(b, i0));
   }
-  // Member solves (FP32: four members each): workgroup w runs on XCD w % 8, so all
-  // members of a problem
-  // go to one XCD and its S stays in that XCD's L2 while they run.  Problems
-  // go, in decreasing order of work, to the XCD with the least work so far;
-  // the eight queues are interleaved and padded with empty entries (-1) to
-  // equal length.
+  // Member solves (or groups of four): workgroup w runs on XCD w % 8, so all
+  // members of a problem go to one XCD and its S stays in that XCD's L2 while
+  // they run.  The eight queues are interleaved and padded with empty entries
+  // (-1) to equal length.
   {
-    constexpr int kXcd = 8;
     std::vector<std::vector<int2>> q(kXcd);
-    std::vector<double> load(kXcd, 0.0);
-    for (int pos = 0; pos < count; ++pos) {
-      const int b = order[pos];
-      int x = 0;
-      for (int t = 1; t < kXcd; ++t)
-        if (load[t] < load[x]) x = t;
-      const int entries = prec == CGD_FP64 ? probs[b].N : batched_groups(probs[b].N);
-      for (int j = 0; j < entries; ++j) q[x].push_back(make_int2(b, j));
-      load[x] += (double)B.mp[b] * B.NP[b] * probs[b].N;
+    for (int b : order) {
+      const int entries = B.members == 4 ? batched_groups(probs[b].N) : probs[b].N;
+      for (int j = 0; j < entries; ++j) q[xcd[b]].push_back(make_int2(b, j));
     }
     size_t len = 0;
     for (const auto& v : q) len = v.size() > len ? v.size() : len;
@@ -878,6 +918,7 @@ cgd_status batch_prepare(int count, const cgd_problem* probs, void* ws, const Ba
   plan->n_gather = B.ngather;
   plan->n_solve = (int)stab.size();
   plan->n_update = B.nupdate;
+  plan->members = B.members;
   plan->off_desc = B.desc;
   plan->off_gtab = B.gtab;
   plan->off_stab = B.stab;
@@ -1217,11 +1258,13 @@ cgd_status cgd_enkf_batched_run(const cgd_batch_plan* plan, void* workspace, dou
   const int2* ut = (const int2*)(base + plan->off_utab);
   const int pc = o.precond == CGD_PRECOND_DIAG_R ? 1 : 0;
   if (plan->prec == CGD_FP64)
-    e = launch_batched<double>((const BProb<double>*)(base + plan->off_desc), gt, plan->n_gather,
-                               st, plan->n_solve, ut, plan->n_update, tol, maxit, pc, err, ev, s);
+    e = launch_batched<double>((const BProb<double>*)(base + plan->off_desc), 1, gt,
+                               plan->n_gather, st, plan->n_solve, ut, plan->n_update, tol, maxit,
+                               pc, err, ev, s);
   else
-    e = launch_batched<float>((const BProb<float>*)(base + plan->off_desc), gt, plan->n_gather,
-                              st, plan->n_solve, ut, plan->n_update, tol, maxit, pc, err, ev, s);
+    e = launch_batched<float>((const BProb<float>*)(base + plan->off_desc), plan->members, gt,
+                              plan->n_gather, st, plan->n_solve, ut, plan->n_update, tol, maxit,
+                              pc, err, ev, s);
   if (e != hipSuccess) return CGD_ERR_HIP;
   if (!stats) return CGD_OK;
   if (hipStreamSynchronize(s) != hipSuccess) return CGD_ERR_HIP;

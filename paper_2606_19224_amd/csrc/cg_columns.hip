@@ -1514,8 +1514,8 @@ __global__ __launch_bounds__(kCB) void k_cg_columns_wide(CGArgs<T> a, ColArgs<T>
 // ---------------------------------------------------------------------------
 // Batched mode: many independent problems, each solved as above (the same
 // per-member recurrence, stop rule and update), in three launches over work
-// tables, so no workgroup ever waits for another (FP32 runs the gather and
-// the solve of cg_batched.hip, four members per workgroup):
+// tables, so no workgroup ever waits for another (FP32 batches that fill the GPU run
+// the gather and the solve of cg_batched.hip, four members per workgroup):
 //   gather  one entry per (problem, block of P.gr padded rows);
 //   solve   one entry per (problem, member), all members of a problem on one
 //           XCD (entries w with w % 8 equal, padding entries -1), problems in
@@ -1806,11 +1806,6 @@ int batched_shape(int m, int N, int* NP, int* mp, int* RL) {
   const int np = col_np<T>(N);
   if (N < 2 || np == 0) return 0;
   *NP = np;
-  if constexpr (sizeof(T) == 4) {  // cg_batched.hip
-    *mp = batched_rows(m);
-    *RL = 0;
-    return np <= 64 && *mp > 0;
-  }
   if (np == 16) batch_shape_np<T, 16>(m, mp, RL);
   else if (np == 32) batch_shape_np<T, 32>(m, mp, RL);
   else batch_shape_np<T, 64>(m, mp, RL);
@@ -1818,15 +1813,17 @@ int batched_shape(int m, int N, int* NP, int* mp, int* RL) {
 }
 
 template <typename T>
-hipError_t launch_batched(const BProb<T>* probs, const int2* gtab, int ngather,
+hipError_t launch_batched(const BProb<T>* probs, int members, const int2* gtab, int ngather,
                           const int2* stab, int nsolve, const int2* utab, int nupdate,
                           double tol, int maxit, int precond, int* err, hipEvent_t* ev,
                           hipStream_t s) {
   hipError_t e;
-  if constexpr (sizeof(T) == 4) {
-    if ((e = launch_bm(probs, gtab, ngather, stab, nsolve, tol, maxit, precond, err, ev, s)) !=
-        hipSuccess)
-      return e;
+  if (members == 4) {
+    if constexpr (sizeof(T) == 4)
+      e = launch_bm(probs, gtab, ngather, stab, nsolve, tol, maxit, precond, err, ev, s);
+    else
+      e = hipErrorInvalidValue;
+    if (e != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(k_bcol_gather<T>, dim3(ngather), dim3(kCB), 0, s, probs, gtab, err,
                        precond);
@@ -1920,10 +1917,10 @@ template hipError_t launch_cg_columns<float>(const CGArgs<float>&, float*, __bf1
                                              hipEvent_t*, hipStream_t);
 template int batched_shape<float>(int, int, int*, int*, int*);
 template int batched_shape<double>(int, int, int*, int*, int*);
-template hipError_t launch_batched<float>(const BProb<float>*, const int2*, int, const int2*, int,
-                                          const int2*, int, double, int, int, int*, hipEvent_t*,
-                                          hipStream_t);
-template hipError_t launch_batched<double>(const BProb<double>*, const int2*, int, const int2*,
+template hipError_t launch_batched<float>(const BProb<float>*, int, const int2*, int, const int2*,
+                                          int, const int2*, int, double, int, int, int*,
+                                          hipEvent_t*, hipStream_t);
+template hipError_t launch_batched<double>(const BProb<double>*, int, const int2*, int, const int2*,
                                            int, const int2*, int, double, int, int, int*,
                                            hipEvent_t*, hipStream_t);
 template hipError_t launch_cg_columns<double>(const CGArgs<double>&, double*, __bf16*,

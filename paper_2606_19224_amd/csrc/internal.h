@@ -126,9 +126,9 @@ struct BProb {
   const T* y;
   const T* rdiag;
   const T* eps;
-  T* Sp;           // S in plane layout, mp x NP (FP32: [NP / 4][mp][4])
-  T* Dt;           // D transposed, N x mp (FP32: unused, D is gathered into Vr)
-  T *Vz, *Vr, *Vp; // CG vectors, N x mp each (FP32: no z; [groups of 4][mp][4])
+  T* Sp;           // S in plane layout, mp x NP (groups of four members: [NP / 4][mp][4])
+  T* Dt;           // D transposed, N x mp (groups: unused, D is gathered into Vr)
+  T *Vz, *Vr, *Vp; // CG vectors, N x mp each (groups: no z; [groups][mp][4])
   T* Rp;           // diag(R) padded with zeros, mp
   double* Wd;      // N * N
   double* col;     // CF_NF * N
@@ -258,7 +258,7 @@ hipError_t launch_cg_tile(const CGArgs<float>& a, int NP, int RB, int variant, h
 constexpr int kBatchRowsDefault = 256;  // rows per gather / update entry unless a problem sets them
 template <typename T>
 int batched_shape(int m, int N, int* NP, int* mp, int* RL);  // 0 when N is out of range
-// FP32 (cg_batched.hip): the solve's entries are (problem, group of four
+// FP32 in groups (cg_batched.hip): the solve's entries are (problem, group of four
 // members); rows padded to a multiple of 64.  launch_bm: the gather and the
 // solve (ev as for launch_batched).
 int batched_groups(int N);
@@ -267,7 +267,7 @@ hipError_t launch_bm(const BProb<float>* probs, const int2* gtab, int ngather, c
                      int nsolve, double tol, int maxit, int precond, int* err, hipEvent_t* ev,
                      hipStream_t s);
 template <typename T>
-hipError_t launch_batched(const BProb<T>* probs, const int2* gtab, int ngather,
+hipError_t launch_batched(const BProb<T>* probs, int members, const int2* gtab, int ngather,
                           const int2* stab, int nsolve, const int2* utab, int nupdate,
                           double tol, int maxit, int precond, int* err, hipEvent_t* ev,
                           hipStream_t s);
