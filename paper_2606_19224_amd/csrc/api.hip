@@ -226,14 +226,12 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       L.tR = take(sizeof(float) * (size_t)m);
     }
   } else {
-    int np = 0, mpad = 0, kc = 0, sc = 0;
-    if (reduced_shape(m, N, (int)esz, &np, &mpad, &kc, &sc)) {
+    int np = 0, mpad = 0;
+    if (reduced_shape(m, N, &np, &mpad)) {
       L.rNP = np;
       L.rmpad = mpad;
-      L.rKC = kc;
-      L.rS = sc;
       const size_t lg = np < 64 ? 64 : (size_t)np, nr = lg;
-      L.rpart = take((size_t)sc * reduced_part_bytes(m, N, (int)esz));  // Q stays on chip
+      L.rpart = take(reduced_parts_bytes(m, N, (int)esz));  // Q stays on chip
       L.rG = take(sizeof(double) * nr * lg);
       L.rWt = take(esz * (size_t)np * np);
       L.rerr = take(sizeof(int) * (size_t)mpad);  // one word per gather workgroup

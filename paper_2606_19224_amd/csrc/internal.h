@@ -283,14 +283,15 @@ template <typename T>
 hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int mode,
                          hipStream_t s, const int* skip = nullptr);
 // Geometry of the reduced mode for N <= 128: N padded to NP (32, 64 or 128), m
-// padded to mpad (a multiple of 32), KC rows per chunk of the N x 2N product
-// and S parts of it (esz: bytes per value).  0 when N is out of range.
-int reduced_shape(int m, int N, int esz, int* NP, int* mpad, int* KC, int* S);
-size_t reduced_part_bytes(int m, int N, int esz);  // one chunk's (or workgroup's) part
-// The same for N > 128: NP a multiple of 64, KC and S as above, mpad rows of Q, which
-// takes kRedPanel rows at a time.  The reduced mode's partial sums without Q held 1024
-// N x 2N parts at most, 16 N^2 KiB: more than a panel of 2^16 rows and its parts for
-// every N > 128, and a panel's launches are then long (268 MB of Q at N = 200).
+// padded to mpad (a multiple of 32); 0 when N is out of range.  reduced_parts_bytes:
+// room for the parts of the N x 2N product (esz: bytes per value).
+int reduced_shape(int m, int N, int* NP, int* mpad);
+size_t reduced_parts_bytes(int m, int N, int esz);
+// The same for N > 128: NP a multiple of 64, KC rows per chunk of the product and S
+// parts of it, mpad rows of Q, which takes kRedPanel rows at a time.  Partial sums
+// without Q, as this mode once had them, held 1024 N x 2N parts at most, 16 N^2 KiB:
+// more than a panel of 2^16 rows and its parts for every N > 128, and a panel's
+// launches are long enough (268 MB of Q at N = 200).
 constexpr int kRedPanel = 1 << 16;
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S);
 // Xg (ng rows) is the array the observations are gathered from; Xf is

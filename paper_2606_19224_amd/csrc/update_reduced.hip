@@ -1,4 +1,5 @@
 // Ensemble update, CGD-EnKF-Reduced and input validation kernels (gfx950).
+#include <algorithm>
 #include <type_traits>
 
 #include "modes.h"
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(kBlock) void k_small_cg(int N, const double* G, con
 // a tall-skinny product over the m rows, summed in parts over row chunks
 // that a later launch adds in a fixed order, with the identity.  Q is built in
 // LDS, 32 rows at a time, and multiplied there: by one workgroup per 32 rows
-// (k_red_pg) while N <= 64 and those are at most 256, else by 256 persistent
+// (k_red_pg) while N <= 64 and those are few (red_streamed), else by 256 persistent
 // workgroups that add their chunks up (k_red_stream).
 // ---------------------------------------------------------------------------
 
@@ -565,19 +566,31 @@ constexpr int kRsRows = 32, kRsThreads = 512, kRsWaves = kRsThreads / 64;
 constexpr int kRsGroups = 256;  // one workgroup per CU
 
 // Past N = 64 always; below, once there are more chunks than workgroups, where
-// a part per chunk costs more than it spreads.
-inline bool red_streamed(int m, int N) {
-  return N > 64 || (m + kRsRows - 1) / kRsRows > kRsGroups;
+// a part per chunk costs more than it spreads: at once in FP64 and for the sEnKF (N =
+// 64, m = 8300: 41.2 against 39.5 us and 25.4 against 20.9), in FP32, whose streamed
+// parts are in double, half as many chunks later (31.1 and 33.6 us at m = 8300, 35.9 and
+// 36.2 at 12000, 45.9 and 42.0 at 20000; N = 32: 24.1 / 24.8, 26.2 / 25.9).
+inline bool red_streamed(int m, int N, int esz, bool sen) {
+  const int most = esz == 4 && !sen ? kRsGroups * 3 / 2 : kRsGroups;
+  return N > 64 || (m + kRsRows - 1) / kRsRows > most;
 }
 // TN at N (as launch_red_stream chooses): two at least.
 inline int red_stream_tiles(int N) { return N <= 32 ? 2 : (N + 15) / 16; }
 
-template <int TN, bool SEN>
+// TS workgroups share a chunk's tiles, each building the chunk for itself: with few
+// chunks one workgroup's tiles are the time (N = 128, whole reduced call, one and four
+// workgroups a chunk: m = 8 28.7 and 26.1 us, m = 600 45.5 and 42.0; FP64 35.7 and 30.5,
+// 61.4 and 56.5).  Past 64 chunks there are workgroups enough.
+template <int TN, bool SEN, int TS>
 struct RsCfg {
   static constexpr int NTL = SEN ? 0 : TN * (TN + 1) / 2;  // left tiles
   static constexpr int NT = NTL + TN * TN;
-  static constexpr int TPW = (NT + kRsWaves - 1) / kRsWaves;  // tiles per wave
+  static constexpr int TPW = (NT + TS * kRsWaves - 1) / (TS * kRsWaves);  // tiles per wave
 };
+constexpr int kRsSplit = 4;
+inline bool red_stream_split(int m, int N) {
+  return N > 64 && (m + kRsRows - 1) / kRsRows * kRsSplit <= kRsGroups;
+}
 // FP32, N <= 64: sums and parts in double, as these sizes added one FP32 part per 32
 // rows in double before they were streamed (m = 10^5, N = 48, relative error of P^T P
 // against 64-bit sums: 2.3e-9 so, 2.1e-8 with FP32 chains over a workgroup's rows).
@@ -592,18 +605,22 @@ inline int red_stream_groups(int m, int N, int esz) {
   if (esz == 4 && N > 64 && nch > kRsChain * g) g = (nch + kRsChain - 1) / kRsChain;
   return nch < g ? nch : g;
 }
+// Parts of the product, streamed or not.
+inline int red_parts(int m, int N, int esz, bool sen) {
+  return red_streamed(m, N, esz, sen) ? red_stream_groups(m, N, esz) : (m + kRsRows - 1) / kRsRows;
+}
 template <typename T, int TN>
 constexpr size_t red_stream_lds() {
   return sizeof(T) * 2 * (size_t)(32 * TN) * (kRsRows + 16 / sizeof(T));
 }
 
-template <typename T, int TN, bool SEN>
+template <typename T, int TN, bool SEN, int TS>
 __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, int k, int nch,
                                                            const T* Xf, const int32_t* idx,
                                                            const T* hw, const T* y,
                                                            const T* rdiag, const T* eps,
                                                            RsPart<T, TN>* part, int* errw) {
-  using C = RsCfg<TN, SEN>;
+  using C = RsCfg<TN, SEN, TS>;
   using P = RsPart<T, TN>;
   constexpr bool FOLD = sizeof(P) > sizeof(T);
   using V = typename Vec4<T>::type;
@@ -719,7 +736,8 @@ __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, 
 
   // ---- this wave's tiles (LDS offsets of their columns) ----
   const int lr = lane & 15, lk = lane >> 4;
-  const int t0 = __builtin_amdgcn_readfirstlane(wv) * C::TPW;
+  const int share = TS > 1 ? blockIdx.y : 0;
+  const int t0 = __builtin_amdgcn_readfirstlane(share * kRsWaves + wv) * C::TPW;
   int ao[C::TPW], bo[C::TPW];
 #pragma unroll
   for (int i = 0; i < C::TPW; ++i) {
@@ -773,7 +791,7 @@ __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, 
     }
   }
   __syncthreads();
-  if (tid == 0) errw[blockIdx.x] = bad;
+  if (tid == 0 && share == 0) errw[blockIdx.x] = bad;
   P* out = part + ((size_t)blockIdx.x * C::NT + t0) * 256;
 #pragma unroll
   for (int i = 0; i < C::TPW; ++i)
@@ -1485,25 +1503,26 @@ hipError_t launch_update(int n, int N, const T* Xf, T* Xa, const double* Wd, int
   return hipGetLastError();
 }
 
-int reduced_shape(int m, int N, int esz, int* NP, int* mpad, int* KC, int* S) {
+int reduced_shape(int m, int N, int* NP, int* mpad) {
   if (N < 2 || N > 128 || m < 1 || m > (1 << 30)) return 0;
   static_assert(kRedFusedRows == kRsRows, "one chunk height");
   const int nch = (m + kRsRows - 1) / kRsRows;
   *NP = N <= 32 ? 32 : N <= 64 ? 64 : 128;
-  *KC = kRsRows;
-  *S = red_streamed(m, N) ? red_stream_groups(m, N, esz) : nch;
   *mpad = nch * kRsRows;
   return 1;
 }
 
 // A part holds all of NP x 2NP from k_red_pg, else its 16 x 16 tiles (RsPart).
-size_t reduced_part_bytes(int m, int N, int esz) {
-  if (!red_streamed(m, N)) {
-    const size_t np = N <= 32 ? 32 : 64;
-    return np * 2 * np * esz;
+size_t reduced_parts_bytes(int m, int N, int esz) {
+  size_t most = 0;
+  for (const bool sen : {false, true}) {
+    const size_t tn = red_stream_tiles(N), np = N <= 32 ? 32 : 64;
+    const size_t part = red_streamed(m, N, esz, sen)
+                            ? (tn * (tn + 1) / 2 + tn * tn) * 256 * (tn <= 4 ? sizeof(double) : esz)
+                            : np * 2 * np * esz;
+    most = std::max(most, part * red_parts(m, N, esz, sen));
   }
-  const size_t tn = red_stream_tiles(N);
-  return (tn * (tn + 1) / 2 + tn * tn) * 256 * (tn <= 4 ? sizeof(double) : esz);
+  return most;
 }
 
 void reduced_wide_shape(int m, int N, int* NP, int* mpad, int* KC, int* S) {
@@ -1567,26 +1586,27 @@ hipError_t launch_red_update_np(int n, int N, const T* Xf, T* Xa, const T* Wt, h
 
 // The two launches of a streamed product: the parts, then their sums (B null: the
 // sEnKF's, into Wt).
-template <typename T, int TN, bool SEN>
+template <typename T, int TN, bool SEN, int TS>
 hipError_t launch_red_stream_tn(int n, int m, int N, int k, const T* Xg, const int32_t* idx,
                                 const T* hw, const T* y, const T* rdiag, const T* eps, void* ws,
                                 const Layout& L, int* iters0, hipStream_t s) {
   using P = RsPart<T, TN>;
-  using C = RsCfg<TN, SEN>;
+  using C = RsCfg<TN, SEN, TS>;
+  const int S = red_parts(m, N, sizeof(T), SEN);
   unsigned char* base = (unsigned char*)ws;
   P* part = (P*)(base + L.rpart);
   int* errw = (int*)(base + L.rerr);
   constexpr size_t lds = red_stream_lds<T, TN>();
-  hipError_t e = hipFuncSetAttribute((const void*)k_red_stream<T, TN, SEN>,
+  hipError_t e = hipFuncSetAttribute((const void*)k_red_stream<T, TN, SEN, TS>,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_red_stream<T, TN, SEN>), dim3(L.rS), dim3(kRsThreads), lds, s, n, m, N, k,
-                     (m + kRsRows - 1) / kRsRows, Xg, idx, hw, y, rdiag, eps, part, errw);
+  hipLaunchKernelGGL((k_red_stream<T, TN, SEN, TS>), dim3(S, TS), dim3(kRsThreads), lds, s, n, m,
+                     N, k, (m + kRsRows - 1) / kRsRows, Xg, idx, hw, y, rdiag, eps, part, errw);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL((k_red_sum_tiles<T, P, SEN>), dim3(C::NT * 8 * sizeof(P) / 16), dim3(kBlock),
-                     0, s, N, TN, L.rNP < 64 ? 64 : L.rNP, L.rS, (const P*)part,
+                     0, s, N, TN, L.rNP < 64 ? 64 : L.rNP, S, (const P*)part,
                      SEN ? nullptr : (double*)(base + L.rG), SEN ? nullptr : (double*)(base + L.rB),
-                     SEN ? (T*)(base + L.rWt) : nullptr, L.rNP, (const int*)errw, L.rS,
+                     SEN ? (T*)(base + L.rWt) : nullptr, L.rNP, (const int*)errw, S,
                      (int*)(base + L.err), iters0);
   return hipGetLastError();
 }
@@ -1595,8 +1615,13 @@ hipError_t launch_red_stream(int n, int m, int N, int k, const T* Xg, const int3
                              const T* hw, const T* y, const T* rdiag, const T* eps, void* ws,
                              const Layout& L, int* iters0, hipStream_t s) {
   auto one = [&](auto tn) {
-    return launch_red_stream_tn<T, decltype(tn)::value, SEN>(n, m, N, k, Xg, idx, hw, y, rdiag,
-                                                             eps, ws, L, iters0, s);
+    constexpr int TN = decltype(tn)::value;
+    if constexpr (TN > 4)
+      if (red_stream_split(m, N))
+        return launch_red_stream_tn<T, TN, SEN, kRsSplit>(n, m, N, k, Xg, idx, hw, y, rdiag, eps,
+                                                          ws, L, iters0, s);
+    return launch_red_stream_tn<T, TN, SEN, 1>(n, m, N, k, Xg, idx, hw, y, rdiag, eps, ws, L,
+                                               iters0, s);
   };
   switch (red_stream_tiles(N)) {
     case 2: return one(std::integral_constant<int, 2>{});
@@ -1626,17 +1651,18 @@ hipError_t launch_reduced_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, c
   int* errw = (int*)(base + L.rerr);
   const int LG = NP < 64 ? 64 : NP, RPL = LG / 64, NR = LG;
   hipError_t e;
-  if (red_streamed(m, N)) {
+  if (red_streamed(m, N, sizeof(T), false)) {
     if ((e = launch_red_stream<T, false>(ng, m, N, k, Xg, idx, hw, y, rdiag, eps, ws, L, nullptr,
                                          s)) != hipSuccess)
       return e;
   } else if constexpr (NP <= 64) {
-    hipLaunchKernelGGL((k_red_pg<T, NP, false>), dim3(L.rS), dim3(kBlock), 0, s, ng, m, N, k, Xg,
+    const int S = red_parts(m, N, sizeof(T), false);
+    hipLaunchKernelGGL((k_red_pg<T, NP, false>), dim3(S), dim3(kBlock), 0, s, ng, m, N, k, Xg,
                        idx, hw, y, rdiag, eps, part, errw);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int nsum = NR * LG + N * N, per = kBlock / 8;
     hipLaunchKernelGGL((k_red_sum2<T, NP>), dim3((nsum + per - 1) / per), dim3(kBlock), 0, s, N,
-                       NR, LG, L.rS, (const T*)part, Gp, B, (const int*)errw, L.rS, err);
+                       NR, LG, S, (const T*)part, Gp, B, (const int*)errw, S, err);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const size_t lds = sizeof(double) * (3 * (kBlock / 64) * (size_t)LG);
@@ -1748,17 +1774,18 @@ hipError_t launch_senkf_mfma(int n, int m, int N, int k, const T* Xf, T* Xa, con
   int* errw = (int*)(base + L.rerr);
   T* Wt = (T*)(base + L.rWt);
   hipError_t e;
-  if (red_streamed(m, N)) {
+  if (red_streamed(m, N, sizeof(T), true)) {
     if ((e = launch_red_stream<T, true>(n, m, N, k, Xf, idx, hw, y, rdiag, eps, ws, L, iters0,
                                         s)) != hipSuccess)
       return e;
   } else if constexpr (NP <= 64) {
-    hipLaunchKernelGGL((k_red_pg<T, NP, true>), dim3(L.rS), dim3(kBlock), 0, s, n, m, N, k, Xf,
+    const int S = red_parts(m, N, sizeof(T), true);
+    hipLaunchKernelGGL((k_red_pg<T, NP, true>), dim3(S), dim3(kBlock), 0, s, n, m, N, k, Xf,
                        idx, hw, y, rdiag, eps, part, errw);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     const int per = kBlock / 8;
     hipLaunchKernelGGL((k_senkf_sum<T, NP>), dim3((NP * NP + per - 1) / per), dim3(kBlock), 0, s,
-                       N, L.rS, (const T*)part, Wt, (const int*)errw, L.rS, err, iters0);
+                       N, S, (const T*)part, Wt, (const int*)errw, S, err, iters0);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
   return launch_red_update_np<T, NP>(n, N, Xf, Xa, Wt, s);
