@@ -43,6 +43,7 @@ sys.path.insert(0, ROOT)
 METRIC = "EnKF analysis steps/sec at rel. residual 1e-6; CG iters & time learned vs plain"
 HBM_PEAK_GBS = 8000.0
 FP32_MFMA_PEAK_TFLOPS = 157.3  # MI355X dense FP32 matrix peak
+FP64_MFMA_PEAK_TFLOPS = 78.6  # MI355X dense FP64 matrix peak
 BF16_MFMA_PEAK_TFLOPS = 2500.0  # MI355X dense BF16 matrix peak (no sparsity)
 
 # HBM traffic per launch of the column solver on the Lorenz-96 twin workload,
@@ -360,12 +361,35 @@ def solver_roofline(info, args, m, N, k, n, it_max):
     flops_alg = np.array([cg_flops(m, N, k, int(i)) for i in it_max])
     tname = 'double' if args.prec == 'fp64' else 'float'
     mfma = False
-    if info["solver"] in ("k_cg_columns", "k_cg_split"):
+    # the gather as a launch of its own ahead of the timed one, which reads S and D back
+    gath = k * m * N * b_x + 8 * m * k + m * N * b_x + 2 * m * N * b_x
+    wide64 = args.prec == "fp64" and N > 64  # these solvers' FP64 forms past N = 64
+    if wide64 and info["solver"] == "k_cg_columns":
+        bytes_alg = bytes_alg - gath + m * N * (b_s + b_x)
+        kernel = (f"k_cg_columns_wide<double> (CG and S^T Z; the update is a launch of its own), "
+                  f"{info['workgroups']} workgroups, one per member")
+        limiter = "each member's pass over S through its CU's path to L2"
+    elif wide64 and info["solver"] == "k_cg_tile":
+        bytes_alg = bytes_alg - gath + m * N * (b_s + b_x)
+        kernel = (f"k_cg_tile64 (CG and S^T Z, both S-products on the 16x16x4 FP64 MFMA, S "
+                  f"resident in LDS), {info['workgroups']} workgroups: groups of 16 members x "
+                  f"blocks of {info['rows_per_block']} rows")
+        limiter = ("the per-iteration reduce-scatter/all-gather of each member group's S^T r, "
+                   "two 64-bit words a double")
+        mfma = True
+    elif info["solver"] in ("k_cg_columns", "k_cg_split"):
         # the gather is a launch of its own ahead of the timed solver launch: the solver
         # reads S and D back instead, and also applies the update (reads X_f, writes X_a)
-        gath = k * m * N * b_x + 8 * m * k + m * N * b_x + 2 * m * N * b_x
         bytes_alg = bytes_alg - gath + m * N * (b_s + b_x) + 2.0 * n * N * b_x
-        if info["solver"] == "k_cg_columns":
+        # few rows: one wave per member (two rows a lane where NP values of S fit 256 bytes)
+        np_ = 16 if N <= 16 else 32 if N <= 32 else 64
+        if info["solver"] == "k_cg_columns" and args.prec in ("fp32", "fp64") and N <= 64 \
+                and m <= (64 if np_ * b_x > 256 else 128):
+            kernel = (f"k_cg_columns_small<{tname}> (CG + S^T Z + ensemble update in one launch), "
+                      f"{info['workgroups']} workgroups, one wave per member")
+            limiter = ("one wave's serial chain of short products, sums, a square root and two "
+                       "divisions per step")
+        elif info["solver"] == "k_cg_columns":
             kernel = (f"k_cg_columns<{tname}> (CG + S^T Z + ensemble update in one launch), "
                       f"{info['workgroups']} workgroups, one per member")
             limiter = ("per-row VALU issue and latency of one workgroup per member (S^T p and "
@@ -611,8 +635,9 @@ def bench_single(args):
     # bounds the kernel (its HBM traffic is the exchange, not S); otherwise the
     # streaming model's bytes against HBM
     # (the mixed kernel's contraction is BF16: its peak is the dense BF16 one)
-    mfma_bound = kname in ("k_cg_tile", "k_cg_tilemx", "k_cg_tilesplit")
-    mpeak = BF16_MFMA_PEAK_TFLOPS if kname in ("k_cg_tilemx", "k_cg_tilesplit") else FP32_MFMA_PEAK_TFLOPS
+    mfma_bound = kname in ("k_cg_tile", "k_cg_tile64", "k_cg_tilemx", "k_cg_tilesplit")
+    mpeak = (BF16_MFMA_PEAK_TFLOPS if kname in ("k_cg_tilemx", "k_cg_tilesplit") else
+             FP64_MFMA_PEAK_TFLOPS if kname == "k_cg_tile64" else FP32_MFMA_PEAK_TFLOPS)
     roof = {
         "bound": "mfma" if mfma_bound else "hbm",
         "kernel": kernel,
@@ -675,13 +700,23 @@ def bench_single(args):
     print(json.dumps(rec), flush=True)
 
 
-def batched_solve_bytes(p, it) -> float:
-    """Algorithmic HBM bytes of one problem in the batched CG launch, FP32,
-    the streaming model of the single-problem solver without its gather:
-    `it` iterations, each reading S twice and moving 8 m x N vectors, then
-    the final S^T Z (S and Z once)."""
+def batched_solve_bytes(p, it, members) -> float:
+    """Bytes one problem of the batched CG launch moves through its workgroups
+    (L2 serves most of them), FP32.  Groups of four members: a first pass over S
+    and r, then `it` steps, each reading S once per group and r, p and diag(R), and
+    writing r and p.  One member a workgroup: S, r, p and diag(R) per member."""
     m, N = p.m, p.N
-    return 4.0 * (it * (2 * m * N + 8 * m * N) + 2 * m * N)
+    if members == 4:
+        groups = (N + 3) // 4
+        return 4.0 * groups * m * ((it + 1) * (N + 1) + 4 * (4 * it + 1))
+    return 4.0 * N * m * ((it + 1) * (N + 1) + 4 * it + 1)
+
+
+def batched_solve_flops(p, it) -> float:
+    """Operations of one problem's solve: S^T d, then two S-products and the vector
+    updates a step for every member."""
+    m, N = p.m, p.N
+    return 2.0 * m * N * N + it * (4.0 * m * N * N + 12.0 * m * N)
 
 
 def bench_batched(args):
@@ -737,8 +772,15 @@ def bench_batched(args):
     solve_ms = np.array([e.elapsed_ms() for e in kev])
     nprob = len(probs)
     value = K * nprob / (ms_total / 1e3)
-    bytes_alg = sum(batched_solve_bytes(p, int(i)) for p, i in zip(probs, it_max))
-    achieved = bytes_alg / (solve_ms.mean() / 1e3) / 1e9
+    members = int(b.plan.members)
+    bytes_alg = sum(batched_solve_bytes(p, int(i), members) for p, i in zip(probs, it_max))
+    flops_alg = sum(batched_solve_flops(p, int(i)) for p, i in zip(probs, it_max))
+    tflops = flops_alg / (solve_ms.mean() / 1e3) / 1e12
+    kernel = ("k_bm_solve (one workgroup per four members of every filter, both S-products on "
+              "the 4x4x1 MFMA); the step also runs k_bm_gather and k_bcol_update" if members == 4
+              else "k_bcol_solve<float> (one workgroup per member of every filter, S-products on "
+              "the VALU); the step also runs k_bcol_gather and k_bcol_update")
+    traffic = measured_traffic("k_bm_solve") if members == 4 and args.count == 256 else None
     rec = {
         "metric": METRIC,
         "value": round(value, 3),
@@ -766,16 +808,20 @@ def bench_batched(args):
         "cg_iters": {"max": int(it_max.max()), "mean_of_max": float(it_max.mean()),
                      "min_of_max": int(it_max.min())},
         "roofline": {
-            "bound": "hbm",
-            "kernel": "k_bm_solve (one workgroup per four members of every filter); the "
-                      "step also runs k_bm_gather and k_bcol_update",
-            "achieved": round(achieved, 2),
-            "peak": HBM_PEAK_GBS,
-            "unit": "GB/s",
-            "frac": round(achieved / HBM_PEAK_GBS, 5),
-            "traffic": measured_traffic("k_bm_solve"),
+            # S stays in L2 and the contractions are the work: the FP32 matrix peak bounds
+            # the launch (the vector ALUs have the same FP32 rate)
+            "bound": "mfma",
+            "kernel": kernel,
+            "achieved": round(tflops, 4),
+            "peak": FP32_MFMA_PEAK_TFLOPS,
+            "unit": "TFLOP/s",
+            "frac": round(tflops / FP32_MFMA_PEAK_TFLOPS, 5),
+            "traffic": traffic,
             "avg_launch_us": round(solve_ms.mean() * 1e3, 2),
-            "alg_bytes_per_launch": float(bytes_alg),
+            "alg_flops_per_launch": float(flops_alg),
+            "bytes_through_workgroups_per_launch": float(bytes_alg),
+            "limiter": "each wave's tile in series: S from L2 to registers and LDS, first "
+                       "product, vector updates, second product",
             "graph_replay_avg_us": round(per_ms.mean() * 1e3, 2),
         },
         "graph_replays_bitwise_equal_eager": bool(repeatable),
