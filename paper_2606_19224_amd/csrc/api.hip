@@ -85,7 +85,9 @@ inline bool prec_tile(int p) { return p == CGD_FP32 || p == CGD_MIXED_BF16 || p 
 
 // FP64, 64 < N <= 128: fewer rows than this stay on the column solver, whose
 // step grows with m (11 us at m = 1024, 18 us at 2048, 51 us at 4093, N = 100)
-// while the row-block solver's is bound by its exchange (16 to 18 us).
+// while the row-block solver's is bound by its exchange (16 to 18 us); the two are
+// even at about this many rows for every N (40 steps at m = 1500, row-block and column
+// solver: 616 and 596 us at N = 72, 636 and 598 at N = 128; 653 to 680 of both at 1800).
 constexpr int kTile64MinRows = 1800;
 // The column solver then takes up to this many rows, past them the streaming solver,
 // which reads S once a step for all members: 20 steps at N = 72 take 23.6 ms there

@@ -1,5 +1,5 @@
-// Batched mode in FP32 (gfx950): the CG of four members of a filter per
-// workgroup, with both S-products on v_mfma_f32_4x4x1_16b_f32.
+// Batched mode in FP32 (gfx950), batches that fill the GPU: the CG of four members
+// of a filter per workgroup, with both S-products on v_mfma_f32_4x4x1_16b_f32.
 //
 // That MFMA forms sixteen 4 x 4 outer products at the rate of the larger FP32
 // shapes, and can broadcast one block's A operand to all sixteen.  With the
@@ -18,9 +18,11 @@
 // S comes from memory once per pass, as [k / 4][row][4] (a lane's 16 bytes, 1
 // KiB per wave load), and goes through the wave's own LDS tile for the second
 // product.  The next tile's loads are in flight during the second product.
-// Chains of FP32 sums stay within one tile (at most 16 terms each way of the
-// four accumulators); tiles and waves are added in double, in a fixed order.
-// No workgroup waits for another.
+// The products' chains of FP32 sums stay within one tile (at most 16 terms each
+// way of the four accumulators); their tiles and waves are added in double, in a
+// fixed order.  The scalar sums (r.r, r.Rr, r.Rp, p.Rp) add a lane's rows in FP32, one
+// a tile of its wave (m / 512 terms; the per-member solver as many or twice that),
+// then lanes and waves in double.  No workgroup waits for another.
 //
 // Bound: the MFMA, LDS and L2 paths of a tile are within a factor of two of
 // each other.  One workgroup per member on the vector ALUs re-read S from L2
@@ -153,7 +155,7 @@ __device__ __attribute__((always_inline)) inline void bm_pass(
     on[m] = STEP && sh.mode[m] == MODE_STEP;
   }
   double gd[4] = {0.0, 0.0, 0.0, 0.0};
-  float sm[4][4];  // (a lane adds one row per tile; lanes and waves in double)
+  float sm[4][4];  // (one row per tile and lane; lanes and waves in double)
 #pragma unroll
   for (int m = 0; m < 4; ++m)
 #pragma unroll
@@ -365,7 +367,7 @@ __global__ __launch_bounds__(kBT) void k_bm_solve(const BProb<float>* probs, con
 
 // Rows [ent.y, ent.y + gr) of a problem: HX (double), S and D = r, both as
 // [chunk of four members][row][4], and diag(R) (0 past m).  NP/4 lanes per row;
-// three row steps' loads in flight.
+// two row steps' loads in flight.
 template <int NP>
 __device__ __attribute__((always_inline)) inline void bm_gather(const BProb<float>& P, int ib, int ie,
                                                                 int precond, int* err) {

@@ -639,100 +639,100 @@ __global__ __launch_bounds__(kRsThreads) void k_red_stream(int n, int m, int N, 
   const int q = tid & 31, rw = tid >> 5;
   int ci[PASS][TB];  // indices (and weights wn) of the next rows
   T wn[PASS][TB], wc[PASS][TB], xv[PASS][TB][4], ev[PASS][4], yv[PASS], rv[PASS];
-      auto load_idx = [&](int ch) __attribute__((always_inline)) {
+  auto load_idx = [&](int ch) __attribute__((always_inline)) {
 #pragma unroll
-        for (int u = 0; u < PASS; ++u) {
-          const int i = ch * kRsRows + u * RPB + rw;
+    for (int u = 0; u < PASS; ++u) {
+      const int i = ch * kRsRows + u * RPB + rw;
 #pragma unroll
-          for (int t = 0; t < TB; ++t) {
-            const bool on = i < m && t < k;
-            ci[u][t] = on ? idx[(size_t)i * k + t] : 0;
-            wn[u][t] = on ? hw[(size_t)i * k + t] : (T)0;
+      for (int t = 0; t < TB; ++t) {
+        const bool on = i < m && t < k;
+        ci[u][t] = on ? idx[(size_t)i * k + t] : 0;
+        wn[u][t] = on ? hw[(size_t)i * k + t] : (T)0;
+      }
+    }
+  };
+  auto load_rows = [&](int ch) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < PASS; ++u) {
+      const int i = ch * kRsRows + u * RPB + rw;
+      const bool live = i < m;
+      yv[u] = live ? y[i] : (T)0;
+      rv[u] = live ? rdiag[i] : (T)1;
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        ev[u][c] = (live && eps && q + 32 * c < N) ? eps[(size_t)i * N + q + 32 * c] : (T)0;
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        wc[u][t] = wn[u][t];
+        if (t < k) {
+          int cx = ci[u][t];
+          if ((unsigned)cx >= (unsigned)n) {  // (rows past m hold index 0, weight 0)
+            if (q == 0) atomicOr(&bad, 2);
+            cx = 0;
+            wc[u][t] = (T)0;
           }
-        }
-      };
-      auto load_rows = [&](int ch) __attribute__((always_inline)) {
-#pragma unroll
-        for (int u = 0; u < PASS; ++u) {
-          const int i = ch * kRsRows + u * RPB + rw;
-          const bool live = i < m;
-          yv[u] = live ? y[i] : (T)0;
-          rv[u] = live ? rdiag[i] : (T)1;
 #pragma unroll
           for (int c = 0; c < 4; ++c)
-            ev[u][c] = (live && eps && q + 32 * c < N) ? eps[(size_t)i * N + q + 32 * c] : (T)0;
-#pragma unroll
-          for (int t = 0; t < TB; ++t) {
-            wc[u][t] = wn[u][t];
-            if (t < k) {
-              int cx = ci[u][t];
-              if ((unsigned)cx >= (unsigned)n) {  // (rows past m hold index 0, weight 0)
-                if (q == 0) atomicOr(&bad, 2);
-                cx = 0;
-                wc[u][t] = (T)0;
-              }
-#pragma unroll
-              for (int c = 0; c < 4; ++c)
-                xv[u][t][c] = q + 32 * c < N ? Xf[(size_t)cx * N + q + 32 * c] : (T)0;
-            }
-          }
+            xv[u][t][c] = q + 32 * c < N ? Xf[(size_t)cx * N + q + 32 * c] : (T)0;
         }
-      };
-      auto finish = [&](int ch, T* buf) __attribute__((always_inline)) {
-        double h[PASS][4];
+      }
+    }
+  };
+  auto finish = [&](int ch, T* buf) __attribute__((always_inline)) {
+    double h[PASS][4];
 #pragma unroll
-        for (int u = 0; u < PASS; ++u)
+    for (int u = 0; u < PASS; ++u)
 #pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            h[u][c] = 0.0;
+      for (int c = 0; c < 4; ++c) {
+        h[u][c] = 0.0;
 #pragma unroll
-            for (int t = 0; t < TB; ++t)
-              if (t < k) h[u][c] += (double)wc[u][t] * (double)xv[u][t][c];
-          }
-        for (int t = TB; t < k; ++t)
+        for (int t = 0; t < TB; ++t)
+          if (t < k) h[u][c] += (double)wc[u][t] * (double)xv[u][t][c];
+      }
+    for (int t = TB; t < k; ++t)
 #pragma unroll
-          for (int u = 0; u < PASS; ++u) {
-            const int i = ch * kRsRows + u * RPB + rw;
-            if (i >= m) continue;
-            const int cx = idx[(size_t)i * k + t];
-            if ((unsigned)cx >= (unsigned)n) {
-              if (q == 0) atomicOr(&bad, 2);
-              continue;
-            }
-            const double w = (double)hw[(size_t)i * k + t];
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-              if (q + 32 * c < N) h[u][c] += w * (double)Xf[(size_t)cx * N + q + 32 * c];
-          }
-#pragma unroll
-        for (int u = 0; u < PASS; ++u) {
-          const int rr = u * RPB + rw;
-          const bool live = ch * kRsRows + rr < m;
-          const double zb = group_sum<32>((h[u][0] + h[u][1]) + (h[u][2] + h[u][3])) / N;
-          double l2 = (double)(N - 1) * (double)rv[u];
-          if constexpr (SEN) {
-            double ss = 0.0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-              if (q + 32 * c < N) ss += (h[u][c] - zb) * (h[u][c] - zb);
-            l2 += group_sum<32>(ss);
-          }
-          const double l = sqrt(l2), yz = (double)yv[u] - zb;
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const int j = q + 32 * c;
-            double pm = 0.0, yt = 0.0;
-            if (live && j < N) {
-              pm = (h[u][c] - zb) / l;
-              yt = (yz + (double)ev[u][c] - (SEN ? h[u][c] - zb : 0.0)) / l;
-            }
-            if (j < 16 * TN) {
-              buf[j * LQ + rr] = (T)pm;
-              buf[(16 * TN + j) * LQ + rr] = (T)yt;
-            }
-          }
+      for (int u = 0; u < PASS; ++u) {
+        const int i = ch * kRsRows + u * RPB + rw;
+        if (i >= m) continue;
+        const int cx = idx[(size_t)i * k + t];
+        if ((unsigned)cx >= (unsigned)n) {
+          if (q == 0) atomicOr(&bad, 2);
+          continue;
         }
-      };
+        const double w = (double)hw[(size_t)i * k + t];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (q + 32 * c < N) h[u][c] += w * (double)Xf[(size_t)cx * N + q + 32 * c];
+      }
+#pragma unroll
+    for (int u = 0; u < PASS; ++u) {
+      const int rr = u * RPB + rw;
+      const bool live = ch * kRsRows + rr < m;
+      const double zb = group_sum<32>((h[u][0] + h[u][1]) + (h[u][2] + h[u][3])) / N;
+      double l2 = (double)(N - 1) * (double)rv[u];
+      if constexpr (SEN) {
+        double ss = 0.0;
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (q + 32 * c < N) ss += (h[u][c] - zb) * (h[u][c] - zb);
+        l2 += group_sum<32>(ss);
+      }
+      const double l = sqrt(l2), yz = (double)yv[u] - zb;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int j = q + 32 * c;
+        double pm = 0.0, yt = 0.0;
+        if (live && j < N) {
+          pm = (h[u][c] - zb) / l;
+          yt = (yz + (double)ev[u][c] - (SEN ? h[u][c] - zb : 0.0)) / l;
+        }
+        if (j < 16 * TN) {
+          buf[j * LQ + rr] = (T)pm;
+          buf[(16 * TN + j) * LQ + rr] = (T)yt;
+        }
+      }
+    }
+  };
 
   // ---- this wave's tiles (LDS offsets of their columns) ----
   const int lr = lane & 15, lk = lane >> 4;
@@ -1310,6 +1310,8 @@ __global__ __launch_bounds__(kBlock) void k_red_sum_wide(int N, int NP, int LG, 
 // 256 fit neither alone.  Every wave carries the whole recurrence and forms
 // its rows' part of q = G p (see k_small_cg_w); the eight parts meet in LDS.
 // Reading G from L2 every step took 378 us for 200 columns, 16 steps; this 38 us.
+// (RR = 24: with 26 rows a wave, N <= 208, nothing spills; with 28 and 32 it is 8 and 11
+// VGPRs, and with 32 the LDS holds no more rows.)
 template <int RPL, int QRows>
 struct SmallCgX {
   static constexpr int LG = 64 * RPL, NW = 8, QR = QRows, RR = 24, RL = QR - RR;

@@ -88,3 +88,14 @@ def test_bad_index_in_either(lib):
         assert b.plan.members == members
         with pytest.raises(lib.CGDError):
             b.run(stats=True)
+
+
+def test_many_rows_in_groups(lib):
+    """One filter of 2 * 10^5 rows in groups of four: 391 rows a lane in its FP32 sums."""
+    p = rounded(W.random_problem(500, 200_000, 40, 1, seed=12, tol=1e-6))
+    b = lib.Batch([_args(p)], prec="fp32", precond="diag_r")
+    assert b.plan.members == 4
+    status, stats = b.run(tol=1e-6, maxit=1000, stats=True)
+    assert status == 0 and stats[0]["n_converged"] == 40
+    ref = O.enkf_reduced(p.Xf, p.idx, p.w, p.y, p.r, p.eps)["Xa"]   # the same analysis
+    assert rel(b.outs[0].cpu().numpy(), ref) <= 1e-4
