@@ -97,7 +97,6 @@ constexpr int kTile64MinRows = 1800;
 constexpr int columns_wide_max(int N) {
   return N < 80 ? 80000 : N < 96 ? 130000 : kColumnsMaxRows;
 }
-constexpr int kWideAppendRows = 1024;  // its buffers may lie behind the others' up to here
 
 Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
   Layout L;
@@ -186,8 +185,8 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       L.gerr = L.xwords ? take(sizeof(int) * (rows / 8 + 1)) : 0;
     }
     // FP64 column solver past N = 64: no other solver's buffers are live with it, so
-    // its own lie on S .. partW when those are large enough, for few rows behind
-    // everything; where they are not (m past about a million) it is not offered
+    // its own lie on S .. partW, which hold them for every m up to about a million;
+    // past that it is not offered
     if (prec == CGD_FP64 && N > 64 && N <= 128 && m <= columns_wide_max(N)) {
       const size_t rows = (size_t)columns_wide_rows(m), sizes[7] = {
           sizeof(double) * rows * 128, sizeof(double) * N * rows, sizeof(double) * N * rows,
@@ -196,13 +195,9 @@ Layout make_layout(int n, int m, int N, int k, int prec, int mode) {
       size_t* offs[7] = {&L.wS, &L.wD, &L.wZ, &L.wR, &L.wP, &L.wRp, &L.wgerr};
       size_t need = 0;
       for (size_t b : sizes) need += al256(b);
-      size_t at = L.S;
-      if (need > L.col - L.S && m <= kWideAppendRows) {
-        at = o;
-        o += need;
-      }
-      if (at != L.S || need <= L.col - L.S) {
+      if (need <= L.col - L.S) {
         L.wrows = (int)rows;
+        size_t at = L.S;
         for (int q = 0; q < 7; ++q) {
           *offs[q] = at;
           at += al256(sizes[q]);
@@ -1414,11 +1409,11 @@ int cgd_layout_selfcheck(int n, int m, int N, int k, int prec) {
     need(L.Ssplit, esz * rows * np);
     need(L.Dsplit, esz * (size_t)N * rows);
   }
-  // FP64 column solver past N = 64: its buffers, one after another, end inside
-  // the partials or the workspace and leave the results alone
+  // FP64 column solver past N = 64: its buffers, one after another, begin at S and
+  // end before the results
   if (L.wrows > 0) {
     const size_t rows = (size_t)L.wrows, end = L.wgerr + sizeof(int) * (rows / 8 + 1);
-    if (L.wS < L.S || end > L.total || (L.wS < L.col && end > L.col)) ++bad;
+    if (L.wS != L.S || end > L.col) ++bad;
     if (L.wrows < m || L.wD - L.wS < 8 * rows * 128 || L.wZ - L.wD < 8 * N * rows ||
         L.wR - L.wZ < 8 * N * rows || L.wP - L.wR < 8 * N * rows ||
         L.wRp - L.wP < 8 * N * rows || L.wgerr - L.wRp < 8 * rows)

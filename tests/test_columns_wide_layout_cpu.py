@@ -1,6 +1,6 @@
 """Workspace of FP64 analyses with 64 < N <= 128: the column solver's buffers lie on
-those of the other solvers, so that past a few rows (kWideAppendRows 1024) the size is
-that of the streaming solver's five m x N arrays and its partial sums, for any m."""
+those of the other solvers, so that the size is that of the streaming solver's five m x N
+arrays and its partial sums, for any m."""
 import ctypes
 
 import pytest
